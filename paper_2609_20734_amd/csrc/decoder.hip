@@ -34,7 +34,6 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
-constexpr int kTile = 8;   // most requests per wavefront in a dense layer
 
 constexpr int kDenseMinWaves = 2048;   // grouping rows stops short of fewer wavefronts than this
 
@@ -73,56 +72,41 @@ struct DenseArgs {
   float eps;
 };
 
-// One wavefront per (group of R output rows, tile of up to T selected
-// requests).  Lanes take 8 consecutive weights of each row (one 16-byte load
-// per row), so a wavefront reads R KiB per 512-element chunk, several chunks
-// in flight; every input load serves all R rows.  The inputs come from cache.
-// The input's sum of squares (for RMSNorm) accumulates in the same pass.
-// Small T keeps registers for loads in flight; R > 1 makes the wavefronts of
-// a layer with many short rows fewer and longer.
-template <bool kSwiGLU, int T, int R>
+// One request per grid row, one wavefront per group of R output rows.  Lanes take 8
+// consecutive weights of each row (one 16-byte load per row), so a wavefront
+// reads R KiB per 512-element chunk, several chunks in flight; every input
+// load serves all R rows.  The inputs come from cache.  The input's sum of
+// squares (for RMSNorm) accumulates in the same pass.  R > 1 makes the
+// wavefronts of a layer with many short rows fewer and longer.
+template <bool kSwiGLU, int R>
 __global__ __launch_bounds__(256) void dense_kernel(DenseArgs p) {
-  constexpr int kAcc = R * T;
-  static_assert(kAcc <= 64, "one result per lane");
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   const int item = blockIdx.x * kWaves + wave;
-  const int groups = p.N / R;                  // the host keeps N a multiple of R
-  const int row0 = (item % groups) * R;
-  const int s0 = (item / groups) * T;
-  const int count = selected_count(p.n_work, p.B);
-  if (s0 >= count) return;
-  const int nb = min(T, count - s0);
-  // a listed request outside [0, B) is computed as request 0 and not stored
-  const int listed = lane < nb ? selected_request(p.work_list, s0 + lane) : 0;
-  const bool my_ok = listed >= 0 && listed < p.B;
-  const int my_req = my_ok ? listed : 0;
-  int req[T];
-#pragma unroll
-  for (int bi = 0; bi < T; ++bi) req[bi] = __shfl(my_req, bi);
+  const int row0 = item * R;                   // the host keeps N a multiple of R
+  if (row0 >= p.N || (int)blockIdx.y >= selected_count(p.n_work, p.B)) return;
+  const int b = selected_request(p.work_list, blockIdx.y);
+  if (b < 0 || b >= p.B) return;               // a listed request outside the batch is skipped
   const bool norm = p.gain != nullptr;
 
+  const float* xr = p.x + (int64_t)b * p.K;
   const uint16_t* wrow = p.W + (int64_t)row0 * p.K;
   const uint16_t* wrow2 = kSwiGLU ? p.W + (int64_t)(p.N + row0) * p.K : nullptr;
-  float acc[R][T], acc2[kSwiGLU ? R : 1][T], ss[T];
+  float acc[R], acc2[kSwiGLU ? R : 1], ss = 0.f;
 #pragma unroll
-  for (int bi = 0; bi < T; ++bi) {
-    ss[bi] = 0.f;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      acc[j][bi] = 0.f;
-      if (kSwiGLU) acc2[j][bi] = 0.f;
-    }
+  for (int j = 0; j < R; ++j) {
+    acc[j] = 0.f;
+    if (kSwiGLU) acc2[j] = 0.f;
   }
   // 512-element chunks (8 per lane).  In a ragged last chunk the lanes past K
   // read element 0 again and weigh it by zero, so every load is unconditional
   // and the loads of successive chunks overlap.
   const int nchunks = (p.K + 511) / 512;
   // about eight 16-byte weight loads in flight per lane; sixteen for the
-  // SwiGLU pair of a single request (few registers per load there, and the
-  // pair is the decoder's largest layer)
+  // SwiGLU pair (few registers per load, and the pair is the decoder's
+  // largest layer)
   constexpr int kRowsPerChunk = kSwiGLU ? 2 * R : R;
-  constexpr int kInFlight = kSwiGLU && T == 1 ? 16 : 8;
+  constexpr int kInFlight = kSwiGLU ? 16 : 8;
   constexpr int kUnroll = kRowsPerChunk >= kInFlight ? 1 : kInFlight / kRowsPerChunk;
 #pragma unroll kUnroll
   for (int c = 0; c < nchunks; ++c) {
@@ -146,56 +130,41 @@ __global__ __launch_bounds__(256) void dense_kernel(DenseArgs p) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) g[e] = 1.f;
     }
+    const float4 x0 = *reinterpret_cast<const float4*>(xr + k);
+    const float4 x1 = *reinterpret_cast<const float4*>(xr + k + 4);
+    const float xv[8] = {x0.x * mask, x0.y * mask, x0.z * mask, x0.w * mask,
+                         x1.x * mask, x1.y * mask, x1.z * mask, x1.w * mask};
 #pragma unroll
-    for (int bi = 0; bi < T; ++bi) {
-      if (bi < nb) {
-        const float* xr = p.x + (int64_t)req[bi] * p.K + k;
-        const float4 x0 = *reinterpret_cast<const float4*>(xr);
-        const float4 x1 = *reinterpret_cast<const float4*>(xr + 4);
-        const float xv[8] = {x0.x * mask, x0.y * mask, x0.z * mask, x0.w * mask,
-                             x1.x * mask, x1.y * mask, x1.z * mask, x1.w * mask};
+    for (int e = 0; e < 8; ++e) {
+      if (norm) ss += xv[e] * xv[e];
+      const float xg = xv[e] * g[e];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (norm) ss[bi] += xv[e] * xv[e];
-          const float xg = xv[e] * g[e];
-#pragma unroll
-          for (int j = 0; j < R; ++j) {
-            const uint32_t we = w[j][e >> 1];
-            acc[j][bi] += ((e & 1) ? bf16_hi(we) : bf16_lo(we)) * xg;
-            if (kSwiGLU) {
-              const uint32_t we2 = w2[j][e >> 1];
-              acc2[j][bi] += ((e & 1) ? bf16_hi(we2) : bf16_lo(we2)) * xg;
-            }
-          }
+      for (int j = 0; j < R; ++j) {
+        const uint32_t we = w[j][e >> 1];
+        acc[j] += ((e & 1) ? bf16_hi(we) : bf16_lo(we)) * xg;
+        if (kSwiGLU) {
+          const uint32_t we2 = w2[j][e >> 1];
+          acc2[j] += ((e & 1) ? bf16_hi(we2) : bf16_lo(we2)) * xg;
         }
       }
     }
   }
 
-  // reduce over the wavefront; lane j * T + bi keeps row row0 + j, request bi
-  float v = 0.f, v2 = 0.f, my_ss = 0.f;
+  // reduce over the wavefront; lane j keeps row row0 + j
+  const float sum_sq = norm ? wave_sum(ss) : 0.f;
+  float v = 0.f, v2 = 0.f;
 #pragma unroll
-  for (int bi = 0; bi < T; ++bi) {
-    if (bi < nb) {
-      const float s = norm ? wave_sum(ss[bi]) : 0.f;
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        const float a = wave_sum(acc[j][bi]);
-        const float a2 = kSwiGLU ? wave_sum(acc2[j][bi]) : 0.f;
-        if (lane == j * T + bi) {
-          v = a;
-          v2 = a2;
-          my_ss = s;
-        }
-      }
+  for (int j = 0; j < R; ++j) {
+    const float a = wave_sum(acc[j]);
+    const float a2 = kSwiGLU ? wave_sum(acc2[j]) : 0.f;
+    if (lane == j) {
+      v = a;
+      v2 = a2;
     }
   }
-  const int j = lane / T, bi = lane % T;
-  const bool ok = __shfl(my_ok ? 1 : 0, bi) != 0;
-  if (lane >= kAcc || bi >= nb || !ok) return;
-  const int b = selected_request(p.work_list, s0 + bi);   // in [0, B): checked above
-  const int row = row0 + j;
-  const float inv = norm ? rsqrtf(my_ss / (float)p.K + p.eps) : 1.f;
+  if (lane >= R) return;
+  const int row = row0 + lane;
+  const float inv = norm ? rsqrtf(sum_sq / (float)p.K + p.eps) : 1.f;
   float out;
   if (kSwiGLU) {
     out = silu(v * inv) * (v2 * inv);
@@ -204,6 +173,311 @@ __global__ __launch_bounds__(256) void dense_kernel(DenseArgs p) {
     if (p.residual) out += p.residual[(int64_t)b * p.N + row];
   }
   p.y[(int64_t)b * p.N + row] = out;
+}
+
+// ---------------------------------------------------------------------------
+// dense layer for several requests, on the matrix cores
+// ---------------------------------------------------------------------------
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMfmaWaves = 8;      // wavefronts per workgroup; they split K
+constexpr int kMfmaRows = 16;      // rows and requests of one MFMA tile
+constexpr int kChunk = 64;         // elements of K a wavefront stages at a time
+constexpr int kMfmaMaxK = 1 << 28; // a tile's sixteen rows stay within 32-bit element offsets
+constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
+
+// x = p[0] + p[1] + p[2] with bf16 pieces, exactly: each piece is the leading
+// eight significant bits of what the ones before it leave (truncation, so no
+// piece overflows).  An infinity is its own first piece; a NaN stays one.
+__device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&p)[3]) {
+  float r[8];
+  float mx = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    r[e] = x[e];
+    mx = fmaxf(mx, fabsf(x[e]));
+  }
+  const bool inf = __any(mx == INFINITY);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)   // the high halves of two floats
+      w[e] = __builtin_amdgcn_perm(__float_as_uint(r[2 * e + 1]), __float_as_uint(r[2 * e]), 0x07060302u);
+    p[q] = __builtin_bit_cast(bf16x8, w);
+    if (q < 2) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r[e] -= __uint_as_float(__float_as_uint(r[e]) & 0xffff0000u);
+      if (q == 0 && inf) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = fabsf(x[e]) == INFINITY ? 0.f : r[e];
+      }
+    }
+  }
+}
+
+// y = W x' for up to 16 selected requests per workgroup on
+// v_mfma_f32_16x16x32_bf16, W's rows as the A operand (lane h, j: row h,
+// elements 8j..8j+7 of a 32-element step) and the requests as columns.  The
+// fp32 inputs enter as three bf16 pieces each (split_bf16x3), so every product
+// is exact and the sums are fp32, as in the one-request kernel; the leading
+// pieces' products and the others' are summed apart, so fewer roundings happen
+// at the size of the result.
+//
+// The eight wavefronts split K into contiguous stretches and add their tiles
+// through LDS in wavefront order.  A wavefront walks its stretch in chunks of
+// kChunk elements, the next chunk's inputs and weights in flight while this
+// one is multiplied.  Both are read as long contiguous runs (inputs: four
+// request rows of 256 bytes per load, weights: eight rows of 128 bytes) and
+// turned into operands through the wavefront's own part of LDS: with each lane
+// reading its operand straight from memory (16 rows of 64 bytes per load,
+// neighbouring lanes on different rows) the loads, not HBM, set the time
+// (2048 -> 151936, 4 requests: 142 us against 106; 6144 -> 2048, 32 requests:
+// 18.5 against 11.7).  The bound is HBM for large layers (2048 -> 151936: 5.8
+// TB/s up to eight requests) and start-up, one wait for the first chunk, and
+// the reduction for small ones.  Two chunks of weights in flight, 16
+// wavefronts, and chunks of 128 were all slower.
+//   P       row tiles of the workgroup (SwiGLU: gate and up tiles each)
+//   kHalf   tiles of eight rows, for at most eight requests at a time: tile
+//           rows and columns 8..15 hold the same rows and requests over the
+//           second half of K (the two off-diagonal quadrants are not used), so
+//           that a layer of few rows still fills the chip
+template <bool kSwiGLU, bool kNorm, int P, bool kHalf>
+__global__ __launch_bounds__(kMfmaWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void dense_mfma_kernel(DenseArgs p) {
+  constexpr int S = kSwiGLU ? 2 * P : P;              // weight streams: stream P + i is tile i's up projection
+  constexpr int kEdge = kHalf ? 8 : kMfmaRows;        // rows and requests per tile
+  constexpr int U = kChunk / 32;                      // steps per chunk
+  constexpr int kLanes = kChunk / 4;                  // lanes that read one input row of a chunk
+  constexpr int kRowsAt = 64 / kLanes;                // input rows per load
+  constexpr int kPairs = kMfmaRows / kRowsAt;         // loads that read a chunk of the sixteen input rows
+  constexpr int kPitch = kChunk + 4;                  // floats per staged input row: rows on different banks
+  constexpr int kWLanes = kChunk / 8;                 // lanes that read one weight row of a chunk
+  constexpr int kWLoads = kMfmaRows * kWLanes / 64;   // loads that read a chunk of one tile
+  constexpr int kWPitch = kChunk + 8;
+  __shared__ union {
+    struct {
+      float x[kMfmaWaves][kMfmaRows][kPitch];
+      uint16_t w[kMfmaWaves][S][kMfmaRows][kWPitch];
+    };
+    f32x4 acc[kMfmaWaves][S][64];
+  } sm;
+  __shared__ float sm_ss[kMfmaWaves][kMfmaRows];
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform(threadIdx.x >> 6);
+  const int h = lane & 15, j = lane >> 4;
+  const int count = selected_count(p.n_work, p.B);
+  // the batch tiles of a row group run next to each other on one XCD
+  // (workgroup i runs on XCD i mod 8), so its weights come from HBM once
+  const int groups = (p.N + P * kEdge - 1) / (P * kEdge);
+  const int span = 8 * ((p.B + kEdge - 1) / kEdge);
+  const int rg = (int)(blockIdx.x / span) * 8 + (int)(blockIdx.x % 8);
+  const int s0 = (int)(blockIdx.x % span) / 8 * kEdge;
+  if (rg >= groups || s0 >= count) return;
+  const int nb = min(kEdge, count - s0);
+  const int row0 = rg * P * kEdge;
+
+  // K in 32-element steps, a contiguous stretch per wavefront; kHalf: tile
+  // rows and columns 8..15 start at the second half
+  const int khalf = kHalf ? ((p.K / 8 + 1) / 2) * 8 : p.K;
+  const int steps = (khalf + 31) / 32;
+  const int per = (steps + kMfmaWaves - 1) / kMfmaWaves;
+  const int step0 = min(steps, wave * per);
+  const int n = min(steps, step0 + per) - step0;
+  const int chunks = (n + U - 1) / U;
+  // end of this wavefront's stretch within either half (kHalf: loads of tile
+  // rows and columns 8..15 take the second)
+  static_assert(!kHalf || (kMfmaRows / kRowsAt == 4 && kWLoads == 2), "a load stays within one half");
+  const int stop0 = min(khalf, (step0 + n) * 32), stop1 = min(p.K - khalf, (step0 + n) * 32);
+
+  // input row 2m + lane / 32 of load m: its request's row (columns past the
+  // last request repeat it and are not stored; a listed request outside
+  // [0, B) is computed as request 0 and not stored) and half of K
+  const float* xrow[kPairs];
+#pragma unroll
+  for (int m = 0; m < kPairs; ++m) {
+    const int v = kRowsAt * m + lane / kLanes;
+    const int b = selected_request(p.work_list, s0 + min(v & (kEdge - 1), nb - 1));
+    xrow[m] = p.x + (int64_t)(b >= 0 && b < p.B ? b : 0) * p.K + (kHalf && m >= kPairs / 2 ? khalf : 0);
+  }
+  // tile row kMfmaRows / kWLoads * i + lane / kWLanes of weight load i, as an
+  // offset from the stream's first row; rows past the last repeat it
+  const uint16_t* wbase[S];
+  uint32_t woff[P][kWLoads];                          // (the host keeps K below kMfmaMaxK)
+#pragma unroll
+  for (int s = 0; s < S; ++s) wbase[s] = p.W + (int64_t)((s < P ? 0 : p.N) + min(row0 + (s % P) * kEdge, p.N - 1)) * p.K;
+#pragma unroll
+  for (int i = 0; i < kWLoads; ++i) {
+    const int v = kMfmaRows / kWLoads * i + lane / kWLanes;
+#pragma unroll
+    for (int s = 0; s < P; ++s)
+      woff[s][i] = (uint32_t)max(0, min(v & (kEdge - 1), p.N - 1 - (row0 + s * kEdge))) * (uint32_t)p.K;
+  }
+  // the epilogue's outputs of this thread; their residuals are read now
+  constexpr int kOut = P * kEdge * kEdge;
+  constexpr int kThreads = kMfmaWaves * 64;
+  constexpr int kPer = (kOut + kThreads - 1) / kThreads;
+  int out_b[kPer];
+  float res[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int e = threadIdx.x + q * kThreads;
+    const int row = row0 + (e / (kEdge * kEdge)) * kEdge + e % kEdge;
+    const int slot = e / kEdge % kEdge;
+    out_b[q] = -1;
+    res[q] = 0.f;
+    if (e < kOut && row < p.N && slot < nb) {
+      const int b = selected_request(p.work_list, s0 + slot);
+      if (b >= 0 && b < p.B) {
+        out_b[q] = b;
+        if (!kSwiGLU && p.residual) res[q] = p.residual[(int64_t)b * p.N + row];
+      }
+    }
+  }
+
+  f32x4 acc[S], low[S];
+  float ss[kPairs];
+#pragma unroll
+  for (int s = 0; s < S; ++s) acc[s] = low[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int m = 0; m < kPairs; ++m) ss[m] = 0.f;
+  u32x4 w[S][kWLoads];
+  f32x4 x[kPairs], g[kHalf ? 2 : 1];
+  const int kx = step0 * 32 + 4 * (lane % kLanes);                                // of chunk 0, within a half
+  const int kw = step0 * 32 + 8 * (lane % kWLanes);
+  // an element past the end reads the row's start; its inputs count as zero
+  auto back_x = [&](int m) { return kHalf && m >= kPairs / 2 ? -khalf : 0; };
+  auto load_x = [&](int c) {
+#pragma unroll
+    for (int m = 0; m < kPairs; ++m) {
+      const int k = kx + c * kChunk;
+      x[m] = *reinterpret_cast<const f32x4*>(xrow[m] + (k < (kHalf && m >= kPairs / 2 ? stop1 : stop0) ? k : back_x(m)));
+    }
+    if (kNorm) {
+#pragma unroll
+      for (int q = 0; q < (kHalf ? 2 : 1); ++q) {
+        const int k = kx + c * kChunk + q * khalf;
+        g[q] = *reinterpret_cast<const f32x4*>(p.gain + (k < p.K ? k : 0));
+      }
+    }
+  };
+  auto load_w = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < kWLoads; ++i) {
+      const int k = kw + c * kChunk;
+      const bool second = kHalf && i == 1;
+      const uint32_t at = k < (second ? stop1 : stop0) ? (uint32_t)(k + (second ? khalf : 0)) : 0u;
+#pragma unroll
+      for (int s = 0; s < S; ++s) w[s][i] = *reinterpret_cast<const u32x4*>(wbase[s] + (woff[s % P][i] + at));
+    }
+  };
+  float (&stage)[kMfmaRows][kPitch] = sm.x[wave];
+  auto put_x = [&](int c) {
+#pragma unroll
+    for (int m = 0; m < kPairs; ++m) {
+      f32x4 v = x[m];
+      if (kx + c * kChunk >= (kHalf && m >= kPairs / 2 ? stop1 : stop0)) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (kNorm) {
+        ss[m] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+        const f32x4 gk = g[kHalf && m >= kPairs / 2 ? 1 : 0];
+        v = f32x4{v[0] * gk[0], v[1] * gk[1], v[2] * gk[2], v[3] * gk[3]};
+      }
+      *reinterpret_cast<f32x4*>(&stage[kRowsAt * m + lane / kLanes][4 * (lane % kLanes)]) = v;
+    }
+  };
+  auto put_w = [&]() {
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+#pragma unroll
+      for (int i = 0; i < kWLoads; ++i)
+        *reinterpret_cast<u32x4*>(&sm.w[wave][s][kMfmaRows / kWLoads * i + lane / kWLanes][8 * (lane % kWLanes)]) = w[s][i];
+    }
+  };
+  auto step = [&](int u) {
+    float xv[8];
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(&stage[h][32 * u + 8 * j]);
+    const f32x4 hi = *reinterpret_cast<const f32x4*>(&stage[h][32 * u + 8 * j + 4]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      xv[e] = lo[e];
+      xv[4 + e] = hi[e];
+    }
+    bf16x8 px[3];
+    split_bf16x3(xv, px);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const bf16x8 ws = *reinterpret_cast<const bf16x8*>(&sm.w[wave][s][h][32 * u + 8 * j]);
+      acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws, px[0], acc[s], 0, 0, 0);
+      low[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws, px[2], low[s], 0, 0, 0);
+      low[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws, px[1], low[s], 0, 0, 0);
+    }
+  };
+  if (chunks > 0) {
+    load_x(0);
+    load_w(0);
+    for (int c = 0; c + 1 < chunks; ++c) {
+      put_x(c);
+      load_x(c + 1);
+      put_w();
+      load_w(c + 1);
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(u);
+    }
+    put_x(chunks - 1);
+    put_w();
+#pragma unroll
+    for (int u = 0; u < U; ++u) step(u);
+  }
+
+  // add the wavefronts' tiles in order
+  if (kNorm) {
+#pragma unroll
+    for (int m = 0; m < kPairs; ++m) {
+#pragma unroll
+      for (int s = kLanes / 2; s >= 1; s >>= 1) ss[m] += __shfl_xor(ss[m], s);
+      if ((lane % kLanes) == 0) sm_ss[wave][kRowsAt * m + lane / kLanes] = ss[m];
+    }
+  }
+  __syncthreads();   // the staged chunks are no longer read
+#pragma unroll
+  for (int s = 0; s < S; ++s) sm.acc[wave][s][lane] = acc[s] + low[s];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    if (out_b[q] < 0) continue;
+    const int e = threadIdx.x + q * kThreads;
+    const int tile = e / (kEdge * kEdge), row = e % kEdge, col = e / kEdge % kEdge;
+    float v = 0.f, v2 = 0.f, sq = 0.f;
+#pragma unroll
+    for (int half = 0; half < (kHalf ? 2 : 1); ++half) {
+      const int hr = row + 8 * half, hcol = col + 8 * half;
+      const int at = (hr / 4) * 16 + hcol;              // the lane that holds rows 4j..4j+3 of the column
+#pragma unroll
+      for (int wv = 0; wv < kMfmaWaves; ++wv) {
+        v += sm.acc[wv][tile][at][hr % 4];
+        if (kSwiGLU) v2 += sm.acc[wv][P + tile][at][hr % 4];
+        if (kNorm) sq += sm_ss[wv][hcol];
+      }
+    }
+    const float inv = kNorm ? rsqrtf(sq / (float)p.K + p.eps) : 1.f;
+    const float out = kSwiGLU ? silu(v * inv) * (v2 * inv) : v * inv + res[q];
+    p.y[(int64_t)out_b[q] * p.N + row0 + tile * kEdge + row] = out;
+  }
+}
+
+template <bool kSwiGLU, int P, bool kHalf>
+oda_status launch_dense_mfma(const DenseArgs& a, hipStream_t stream) {
+  constexpr int kEdge = kHalf ? 8 : kMfmaRows;
+  const int64_t groups = oda::ceil_div(oda::ceil_div(a.N, P * kEdge), 8) * 8 * oda::ceil_div(a.B, kEdge);
+  if (groups > INT_MAX) return oda::fail(ODA_ERR_SHAPE, "layer too large");
+  const dim3 grid((unsigned)groups), block(kMfmaWaves * 64);
+  if (a.gain)
+    hipLaunchKernelGGL((dense_mfma_kernel<kSwiGLU, true, P, kHalf>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((dense_mfma_kernel<kSwiGLU, false, P, kHalf>), grid, block, 0, stream, a);
+  return ODA_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -406,52 +680,60 @@ extern "C" oda_status oda_dense_bf16(const oda_dense_desc* desc, int32_t batch, 
   if (!(desc->rms_eps >= 0.f) || !std::isfinite(desc->rms_eps)) return oda::fail(ODA_ERR_SHAPE, "rms_eps must be >= 0");
   if (!oda::aligned(desc->weight, 16) || !oda::aligned(x, 16) || (desc->norm_gain && !oda::aligned(desc->norm_gain, 16)))
     return oda::fail(ODA_ERR_SHAPE, "weight, x and norm_gain must be 16-byte aligned");
-  // requests per wavefront: one, up to four, or up to eight; then the most
-  // rows per wavefront that still leave >= kDenseMinWaves wavefronts
-  const int tile = batch == 1 ? 1 : batch <= 4 ? 4 : kTile;
-  const int64_t tiles = oda::ceil_div(batch, tile);
   const int N = desc->out_features;
   const bool swiglu = desc->mode == ODA_DENSE_SWIGLU;
-  const int rmax = swiglu ? (tile == 1 ? 4 : 2) : (tile == 1 ? 8 : tile == 4 ? 4 : 2);
+  DenseArgs a{desc->weight, desc->norm_gain, x, residual, y, work_list, n_work, N, desc->in_features, batch,
+              desc->rms_eps};
+  (void)hipGetLastError();
+  // Several requests: the narrowest workgroup (row tiles and tile edge) that
+  // still needs no more than one per CU, so that the launch is one even round;
+  // layers too large for that take the widest.  Narrower ones re-split and
+  // re-read the inputs more often, wider ones leave CUs idle: 6144 -> 2048, 8
+  // requests 7.4 us with 8-row workgroups against 10.6 with 16, 32 requests
+  // 11.7 with 16 against 19.9 with 8; gate and up 2048 -> 6144, 32 requests
+  // 16.6 with 48 rows, 21.6 with 32, 19.9 with 16.  A layer of many rounds
+  // takes this path for one request too (2048 -> 151936: 104 us against 110).
+  const auto groups_of = [&](int tiles, int edge) {
+    return oda::ceil_div(N, tiles * edge) * oda::ceil_div(batch, edge);
+  };
+  if ((batch > 1 || (!swiglu && groups_of(2, kMfmaRows) >= 8 * kTargetGroups)) && a.K < kMfmaMaxK) {
+    oda_status st;
+    const auto fits = [&](int tiles, int edge) { return groups_of(tiles, edge) <= kTargetGroups; };
+    if (swiglu) {
+      if (fits(1, 8)) st = launch_dense_mfma<true, 1, true>(a, stream);
+      else if (fits(2, 8)) st = launch_dense_mfma<true, 2, true>(a, stream);
+      else if (fits(3, 8)) st = launch_dense_mfma<true, 3, true>(a, stream);
+      else if (fits(1, kMfmaRows)) st = launch_dense_mfma<true, 1, false>(a, stream);
+      else if (fits(2, kMfmaRows)) st = launch_dense_mfma<true, 2, false>(a, stream);
+      else st = launch_dense_mfma<true, 3, false>(a, stream);
+    } else {
+      if (fits(1, 8)) st = launch_dense_mfma<false, 1, true>(a, stream);
+      else if (fits(2, 8)) st = launch_dense_mfma<false, 2, true>(a, stream);
+      else if (fits(1, kMfmaRows)) st = launch_dense_mfma<false, 1, false>(a, stream);
+      else st = launch_dense_mfma<false, 2, false>(a, stream);
+    }
+    return st == ODA_OK ? launch_status() : st;
+  }
+  // one request (or rows too long for the tiles): the most rows per wavefront
+  // that still leave >= kDenseMinWaves wavefronts
   int rows = 1;
-  for (int r = rmax; r > 1; r /= 2)
-    if (N % r == 0 && (int64_t)(N / r) * tiles >= kDenseMinWaves) {
+  for (int r = swiglu ? 4 : 8; r > 1; r /= 2)
+    if (N % r == 0 && N / r >= kDenseMinWaves) {
       rows = r;
       break;
     }
-  const int64_t groups = oda::ceil_div((int64_t)(N / rows) * tiles, kWaves);
-  if (groups > INT_MAX) return oda::fail(ODA_ERR_SHAPE, "layer too large");
-  DenseArgs a{desc->weight, desc->norm_gain, x, residual, y, work_list, n_work, N, desc->in_features, batch,
-              desc->rms_eps};
-  const dim3 grid((unsigned)groups), block(256);
-  (void)hipGetLastError();
-#define ODA_DENSE_LAUNCH(SW, T, R) hipLaunchKernelGGL((dense_kernel<SW, T, R>), grid, block, 0, stream, a)
+  const int64_t groups = oda::ceil_div(N / rows, kWaves);
+  const dim3 grid((unsigned)groups, (unsigned)batch), block(256);
+#define ODA_DENSE_LAUNCH(SW, R) hipLaunchKernelGGL((dense_kernel<SW, R>), grid, block, 0, stream, a)
   if (swiglu) {
-    if (tile == 1) {
-      if (rows == 4) ODA_DENSE_LAUNCH(true, 1, 4);
-      else if (rows == 2) ODA_DENSE_LAUNCH(true, 1, 2);
-      else ODA_DENSE_LAUNCH(true, 1, 1);
-    } else if (tile == 4) {
-      if (rows == 2) ODA_DENSE_LAUNCH(true, 4, 2);
-      else ODA_DENSE_LAUNCH(true, 4, 1);
-    } else {
-      if (rows == 2) ODA_DENSE_LAUNCH(true, kTile, 2);
-      else ODA_DENSE_LAUNCH(true, kTile, 1);
-    }
+    if (rows == 4) ODA_DENSE_LAUNCH(true, 4);
+    else if (rows == 2) ODA_DENSE_LAUNCH(true, 2);
+    else ODA_DENSE_LAUNCH(true, 1);
   } else {
-    if (tile == 1) {
-      if (rows == 8) ODA_DENSE_LAUNCH(false, 1, 8);
-      else if (rows == 4) ODA_DENSE_LAUNCH(false, 1, 4);
-      else if (rows == 2) ODA_DENSE_LAUNCH(false, 1, 2);
-      else ODA_DENSE_LAUNCH(false, 1, 1);
-    } else if (tile == 4) {
-      if (rows == 4) ODA_DENSE_LAUNCH(false, 4, 4);
-      else if (rows == 2) ODA_DENSE_LAUNCH(false, 4, 2);
-      else ODA_DENSE_LAUNCH(false, 4, 1);
-    } else {
-      if (rows == 2) ODA_DENSE_LAUNCH(false, kTile, 2);
-      else ODA_DENSE_LAUNCH(false, kTile, 1);
-    }
+    if (rows == 8) ODA_DENSE_LAUNCH(false, 8);
+    else if (rows == 4) ODA_DENSE_LAUNCH(false, 4);
+    else if (rows == 2) ODA_DENSE_LAUNCH(false, 2);
+    else ODA_DENSE_LAUNCH(false, 1);
   }
 #undef ODA_DENSE_LAUNCH
   return launch_status();
