@@ -52,9 +52,14 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kBlock = 16;            // positions per KV block
 constexpr int kMaxGroup = 16;         // query heads per KV head held by one MFMA tile
 constexpr int kWaves = 8;             // wavefronts per split workgroup
-constexpr int kTargetGroups = 256;    // workgroups a call aims for (one per CU)
+constexpr int kTargetShift = 8;
+constexpr int kTargetGroups = 1 << kTargetShift;   // workgroups a call aims for (one per CU)
 constexpr int kBalanceBlocks = 512;   // shortest split the plan adds to even out the CUs
 constexpr int kBalanceUnits = 64;     // units per request from which the plan evens out the CUs
+constexpr int kLengthBlocks = 128;    // below that: shortest split that the plan by length adds rounds for
+constexpr int kLengthRounds = 16;     // rounds of workgroups it considers
+constexpr int kLongBlocks = 1024;     // blocks per CU from which its splits are kLongSplit blocks
+constexpr int kLongSplit = 512;
 constexpr int kMergeChunk = 16;       // split partials read per round trip in the merge
 constexpr int kMergeSmall = 4;        // chunk used for the last few splits
 constexpr float kLog2e = 1.4426950408889634f;
@@ -87,6 +92,8 @@ struct AttnArgs {
   int32_t dyn_splits;       // 1: blocks per split chosen on the device (effective_bps)
   int32_t split_cap;        // most splits per unit the automatic plan considers
   int32_t nvb_max;          // host bound on visited blocks per request
+  int32_t by_length;        // Full: splits chosen on the device from the selected requests' lengths (length_plan)
+  int32_t pair_slots;       // (request, split) pairs the grid covers
   int32_t lpi;              // layers per work item (attn_local_layers_kernel)
   int32_t select;
   float scale_log2;         // scale * log2(e)
@@ -103,7 +110,7 @@ struct AttnArgs {
   const float* k_gain;   // [D] or NULL
   uint16_t* k_out;       // [B][Hkv][D]: the candidate K (bf16) for the commit, or NULL
   uint16_t* v_out;       // [B][Hkv][D]
-  double rope_theta;
+  double rope_log2_theta;
   float rms_eps;
   // direct-ring Local: the window is read from per-unit rings of whole blocks
   // (k_ring [L][B][SB + RB][Hkv][D/8][16][8], v_ring alike) instead of the
@@ -225,15 +232,15 @@ __device__ __forceinline__ bool request_of_rank(const AttnArgs& a, int rank, int
 // units * s <= 256 m is taken as soon as it fills the CUs within 10% of
 // evenly; if no count up to `cap` does, the most even one.  At most 17 steps,
 // the same on the host (plan) and on the device (selected requests).
-__host__ __device__ __forceinline__ int64_t balanced_splits(int64_t units, int64_t want, int64_t cap) {
+__host__ __device__ __forceinline__ uint32_t balanced_splits(uint32_t units, uint32_t want, uint32_t cap) {
   if (want >= cap) return cap;
-  int64_t best = want;
-  int64_t best_m = (units * want + kTargetGroups - 1) / kTargetGroups;   // workgroups per CU at `want`
-  for (int64_t m = best_m; m <= best_m + 16; ++m) {
-    const int64_t s = kTargetGroups * m / units;
+  uint32_t best = want;
+  uint32_t best_m = (uint32_t)(((uint64_t)units * want + kTargetGroups - 1) >> kTargetShift);   // workgroups per CU at `want`
+  for (uint32_t m = best_m; m <= best_m + 16; ++m) {
+    const uint32_t s = kTargetGroups * m / units;
     if (s > cap) break;
-    if (kTargetGroups * m * 10 <= units * s * 11) return s;
-    if (m * best < best_m * s) {   // m / s below best_m / best: more even
+    if ((uint64_t)kTargetGroups * m * 10 <= (uint64_t)units * s * 11) return s;
+    if ((uint64_t)m * best < (uint64_t)best_m * s) {   // m / s below best_m / best: more even
       best = s;
       best_m = m;
     }
@@ -252,21 +259,153 @@ __host__ __device__ __forceinline__ int64_t balanced_splits(int64_t units, int64
 // units of one request; when a request has fewer than kBalanceUnits of them
 // (one-layer calls), the spread of the requests' lengths sets the balance
 // instead, and more splits made per-layer calls over 8K-64K requests slower.
-__host__ __device__ __forceinline__ int plan_bps(int64_t units, int64_t per_request, int nvb_max, int cap) {
-  const int64_t want = (kTargetGroups + units - 1) / units;
-  int64_t s = want < cap ? want : cap;
-  const int64_t keep = nvb_max / kBalanceBlocks;   // splits that keep kBalanceBlocks blocks each
-  if (per_request >= kBalanceUnits && keep > s) s = balanced_splits(units, s, keep < cap ? keep : cap);
+// Units and split counts fit 32 bits (the grid does), and the divisions are
+// 32-bit ones: the device runs this before its first read of a request.
+__host__ __device__ __forceinline__ int plan_bps(uint32_t units, uint32_t per_request, int nvb_max, int cap) {
+  const uint32_t want = ((uint32_t)kTargetGroups + units - 1) / units;
+  uint32_t s = want < (uint32_t)cap ? want : (uint32_t)cap;
+  const uint32_t keep = (uint32_t)nvb_max / kBalanceBlocks;   // splits that keep kBalanceBlocks blocks each
+  if (per_request >= (uint32_t)kBalanceUnits && keep > s)
+    s = balanced_splits(units, s, keep < (uint32_t)cap ? keep : (uint32_t)cap);
   if (s < 1) s = 1;
-  const int bps = (int)(((nvb_max + s - 1) / s + 1) & ~(int64_t)1);
+  const int bps = (int)(((uint32_t)nvb_max / s + ((uint32_t)nvb_max % s != 0 ? 1 : 0) + 1) & ~1u);
   return bps > 2 ? bps : 2;
 }
 
 // Blocks per split for this call: fixed by the caller, or the automatic plan
-// for the number of selected requests (known only on the device for Full).
+// for the number of selected requests, known only on the device when a list
+// or flags select them (the host's a.bps covers all B).
 __device__ __forceinline__ int effective_bps(const AttnArgs& a, int active) {
-  if (!a.dyn_splits) return a.bps;
-  return uniform(plan_bps((int64_t)max(active, 1) * a.L * a.Hkv, (int64_t)a.L * a.Hkv, a.nvb_max, a.split_cap));
+  if (!a.dyn_splits || a.select == kSelAll) return a.bps;
+  const uint32_t per_request = (uint32_t)a.L * (uint32_t)a.Hkv;
+  return uniform(plan_bps((uint32_t)max(active, 1) * per_request, per_request, a.nvb_max, a.split_cap));
+}
+
+// Inclusive scan over the wavefront in six DPP steps (row shifts by 1, 2, 4,
+// 8, then each row's last lane into the next row, then the lower half's into
+// the upper): lane 63 holds the reduction.  Identity 0.
+template <bool kMax>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+  const auto op = [](uint32_t p, uint32_t q) { return kMax ? (p > q ? p : q) : p + q; };
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<false>(x), 63);
+}
+__device__ __forceinline__ uint32_t even_up(uint32_t x) { return (x + 1) & ~1u; }
+
+// One work item of a Full call: request, its length, its split of nsplit, and
+// the blocks per split.
+struct Item {
+  int b, n, split, nsplit, bps;
+};
+
+// Blocks per split for up to 64 selected requests of nvb blocks each (per
+// lane; 0 where not selected or invalid) with `units` (layer, KV head) units
+// apiece.  Wavefront-uniform; the same in every workgroup of the call.
+//   - eight units per CU, whole units that fill their rounds of one workgroup
+//     per CU within 5%, or one round whose longest unit takes no longer alone
+//     (0.18 us a 128-wide block) than all blocks on a busy HBM (0.29 us a block
+//     and CU) and the merge (8 us): whole units.  24 requests of 200-2,000
+//     positions: 27.9 us, 35.8 split;
+//   - kLongBlocks blocks per CU: splits of kLongSplit blocks, whatever rounds
+//     that makes.  Many uneven rounds beat few even ones, whose workgroups
+//     start and wait for their first blocks together: one layer of 32
+//     requests of 8K-64K positions 721 us, in eight even rounds
+//     812, with the longest request's splits for all 913;
+//   - else, for m = 1, 2, ... rounds, the shortest splits whose (request,
+//     split) pairs fit m rounds; the first m at which they spread the blocks
+//     over the CUs within 10% of evenly, else the m with the least m * bps.
+//     Rounds past the first feasible one are tried only while splits keep
+//     kLengthBlocks blocks.
+template <int D>
+__device__ __forceinline__ uint32_t length_bps(const AttnArgs& a, uint32_t nvb, bool selected, uint32_t units) {
+  const uint32_t total = wave_total(nvb);
+  const uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<true>(nvb), 63);
+  const uint32_t count = (uint32_t)__popcll(__ballot(selected));
+  const uint32_t whole = even_up(max(longest, 2u));
+  const uint64_t work = (uint64_t)total * units;
+  const uint32_t rounds = (count * units + kTargetGroups - 1) >> kTargetShift;
+  if (rounds >= 8 || work * 20 >= ((uint64_t)rounds * whole << kTargetShift) * 19) return whole;
+  if (rounds == 1 && ((uint64_t)whole * 5 << kTargetShift) <= 8 * work + ((uint64_t)(240 * 128 / D) << kTargetShift)) return whole;
+  // no split shorter than a block per wavefront, no more splits than partial slots
+  const uint32_t least = even_up(max((uint32_t)kWaves, (longest + (uint32_t)a.max_splits - 1) / (uint32_t)a.max_splits));
+  const auto fits = [&](uint32_t c, uint32_t pairs) {
+    return wave_total(selected ? max(1u, (nvb + c - 1) / c) : 0u) <= pairs;
+  };
+  // the shortest splits that fit `pairs` (at bps there are at most total / bps + count)
+  const auto fit = [&](uint32_t pairs) {
+    for (uint32_t j = 0; j <= 3; ++j) {
+      const uint32_t room = 4 * pairs - j * count;
+      const uint32_t c = min(whole, max(least, even_up((4 * total + room - 1) / room)));
+      if (fits(c, pairs)) return c;
+    }
+    return whole;
+  };
+  const uint32_t slots = (uint32_t)a.pair_slots;
+  if (work >= (uint64_t)kLongBlocks << kTargetShift) {
+    const uint32_t c = min(whole, max(least, (uint32_t)kLongSplit));
+    return fits(c, slots) ? c : fit(slots);
+  }
+  uint32_t best = whole, best_m = 0;
+  for (uint32_t m = 1; m <= (uint32_t)kLengthRounds; ++m) {
+    const uint32_t pairs = min((uint32_t)kTargetGroups * m / units, slots);
+    if (pairs < count) continue;
+    if (best_m != 0 && work < ((uint64_t)kLengthBlocks * m << kTargetShift)) break;
+    const uint32_t c = fit(pairs);
+    if (best_m == 0 || m * c < best_m * best) {
+      best = c;
+      best_m = m;
+    }
+    if (work * 10 >= ((uint64_t)m * c << kTargetShift) * 9) break;
+  }
+  return best;
+}
+
+// The item of (request, split) pair `pair` of a Full call planned from the
+// selected requests' lengths: lane i holds the i-th listed request (list) or
+// request i (flags, all), the pairs are numbered request by request without
+// gaps, so that the workgroups with work form a prefix of the grid (gaps make
+// the dispatcher pile live workgroups onto part of the CUs).  False past the
+// last pair.
+template <int D>
+__device__ __forceinline__ bool length_item(const AttnArgs& a, int active, uint32_t pair, Item& it) {
+  const int lane = (int)(threadIdx.x & 63);
+  int b = lane;
+  bool selected;
+  if (a.select == kSelList) {
+    selected = lane < active;
+    b = selected ? a.work_list[lane] : -1;
+    selected = b >= 0 && b < a.B;
+  } else {
+    selected = lane < a.B;
+    if (a.select == kSelFlags) selected = selected && a.flags[lane] != 0;
+  }
+  const int n = selected ? a.seq_lens[b] : 0;
+  uint32_t nvb = 0;
+  if (selected && n >= 1 && n <= a.max_len) nvb = (uint32_t)geometry(n, 0, a.window, a.has_cur).nvb;
+  uint32_t bps = length_bps<D>(a, nvb, selected, (uint32_t)a.L * (uint32_t)a.Hkv);
+  uint32_t splits = selected ? max(1u, (nvb + bps - 1) / bps) : 0u;
+  if (splits > 1) {   // a request's splits of equal length
+    bps = even_up((nvb + splits - 1) / splits);
+    splits = (nvb + bps - 1) / bps;
+  }
+  const uint32_t upto = wave_scan<false>(splits);
+  const uint64_t before = __ballot(upto <= pair);
+  if (before == ~0ull) return false;
+  const int at = (int)__popcll(before);
+  it.b = __builtin_amdgcn_readlane(b, at);
+  it.n = __builtin_amdgcn_readlane(n, at);
+  it.nsplit = __builtin_amdgcn_readlane((int)splits, at);
+  it.bps = __builtin_amdgcn_readlane((int)bps, at);
+  it.split = (int)pair - (__builtin_amdgcn_readlane((int)upto, at) - it.nsplit);
+  return true;
 }
 
 __device__ __forceinline__ bf16x8 load16(const uint16_t* p) {
@@ -459,48 +598,76 @@ __host__ __device__ constexpr size_t split_lds_floats(int G, int D) {
 // A fused call's bf16 query rows and candidate K/V, after the floats above.
 __host__ __device__ constexpr size_t prep_lds_bytes(int G, int D) { return (size_t)(G + 2) * D * 2; }
 
-// Running state of one output element of the split merge: maximum logit M
-// (log2 units), weighted sum of partial outputs and of partial denominators.
+// Split partials pass between workgroups on different XCDs, whose L2 caches
+// are not coherent with each other: they are written and read as 8-byte
+// relaxed atomics at device scope (write-through stores, loads that bypass
+// the caches), so publishing them needs no write-back of an L2 and reading
+// them no invalidate.
+__device__ __forceinline__ void publish2(float* p, float x, float y) {
+  const uint64_t v = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 published2(const float* p) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+// Running state of two neighbouring output elements of the split merge:
+// maximum logit M (log2 units), weighted sums of partial outputs and of
+// partial denominators.
 struct MergeAcc {
-  float M = -INFINITY, acc = 0.f, lam = 0.f;
+  float M = -INFINITY, lam = 0.f, acc0 = 0.f, acc1 = 0.f;
 };
 
-// Fold splits [s0, s0 + C) of one (query head hh, dimension d) into m; indices
-// past the last split repeat it with weight 0.
+__device__ __forceinline__ void merge_rescale(MergeAcc& m, float M) {
+  const float r = (M == m.M) ? 1.f : exp2_fast(m.M - M);
+  m.acc0 *= r;
+  m.acc1 *= r;
+  m.lam *= r;
+  m.M = M;
+}
+
+// Fold splits [s0, min(s0 + C, s_end)) of query head hh, dimensions d and
+// d + 1 into m (s0 < s_end); indices past the last split repeat it with
+// weight 0.
 template <int C, int D>
-__device__ __forceinline__ void merge_chunk(MergeAcc& m, const float* ml, const float* po, int s0, int nsplit,
+__device__ __forceinline__ void merge_chunk(MergeAcc& m, const float* ml, const float* po, int s0, int s_end,
                                             int G, int hh, int d) {
-  float mv[C], lv[C], ov[C];
+  float2 mlv[C], ov[C];
 #pragma unroll
   for (int k = 0; k < C; ++k) {
-    const int s = min(s0 + k, nsplit - 1);
-    mv[k] = ml[(s * G + hh) * 2];
-    lv[k] = ml[(s * G + hh) * 2 + 1];
-    ov[k] = po[((int64_t)s * G + hh) * D + d];
+    const int s = min(s0 + k, s_end - 1);
+    mlv[k] = published2(ml + ((int64_t)s * G + hh) * 2);
+    ov[k] = published2(po + ((int64_t)s * G + hh) * D + d);
   }
   float Mc = m.M;
 #pragma unroll
-  for (int k = 0; k < C; ++k) Mc = fmaxf(Mc, mv[k]);
-  const float r = (Mc == m.M) ? 1.f : exp2_fast(m.M - Mc);
-  m.acc *= r;
-  m.lam *= r;
-  m.M = Mc;
+  for (int k = 0; k < C; ++k) Mc = fmaxf(Mc, mlv[k].x);
+  merge_rescale(m, Mc);
 #pragma unroll
   for (int k = 0; k < C; ++k) {
-    const float w = (s0 + k < nsplit) ? exp2_fast(mv[k] - Mc) : 0.f;
-    m.acc += w * ov[k];
-    m.lam += w * lv[k];
+    const float w = (s0 + k < s_end) ? exp2_fast(mlv[k].x - Mc) : 0.f;
+    m.acc0 += w * ov[k].x;
+    m.acc1 += w * ov[k].y;
+    m.lam += w * mlv[k].y;
   }
 }
 
 // Combine the nsplit partials of one (layer, request, KV head) with stable
 // softmax rescaling (plus the uncommitted candidate) and write out / lse.
-// Called by every thread of a workgroup of `nthreads` threads (it holds a
-// barrier); sm_zc: LDS for kMaxGroup candidate logits.  Partials are read in
-// split order, so the result does not depend on which workgroup merges.
+// Called by every thread of a split workgroup (it holds barriers); sm_zc: LDS
+// for kMaxGroup candidate logits; sm_part: LDS of kWaves * G * D floats.  A
+// thread takes two neighbouring output elements of a contiguous range of the
+// splits (up to four ranges, as many as the threads allow), and the ranges'
+// sums are added in order, so the result does not depend on which workgroup
+// merges.  Every partial is a trip to memory: with the ranges, up to 64
+// splits of four query heads (128 of two) are two loads deep per thread and
+// one trip, where one thread per element and all splits took one trip per 16.
 template <int D>
 __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int g, int nsplit, float* sm_zc,
-                                           int nthreads, const CurSrc& cur) {
+                                           float* sm_part, const CurSrc& cur) {
+  constexpr int kThreads = kWaves * 64;
   const int G = a.G;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -514,7 +681,7 @@ __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int 
     float kc[PD];
 #pragma unroll
     for (int e = 0; e < PD; ++e) kc[e] = bf16_to_float(cur.k[lane * PD + e]);
-    for (int hh = wave; hh < G; hh += nthreads / 64) {
+    for (int hh = wave; hh < G; hh += kWaves) {
       float dot = 0.f;
 #pragma unroll
       for (int e = 0; e < PD; ++e) dot += bf16_to_float(cur.q[hh * D + lane * PD + e]) * kc[e];
@@ -522,29 +689,48 @@ __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int 
       if (lane == 0) sm_zc[hh] = dot;
     }
   }
-  __syncthreads();
 
-  // The partials were written back from other XCDs, so every read is a trip to
-  // memory: a chunk of splits is loaded with all its reads in flight at once,
-  // and the running maximum is rescaled once per chunk.
-  for (int e = threadIdx.x; e < G * D; e += nthreads) {
+  const int pairs = G * D / 2;                                       // element pairs of the unit
+  const int ranges = max(1, min(min(4, kThreads / pairs), nsplit));   // split ranges merged side by side
+  const int per = (nsplit + ranges - 1) / ranges;
+  float4* part = reinterpret_cast<float4*>(sm_part);                 // [ranges][pairs]: M, lam, acc0, acc1
+  for (int i = threadIdx.x; i < ranges * pairs; i += kThreads) {
+    const int range = i / pairs, e = 2 * (i - range * pairs);
+    const int hh = e / D, d = e - hh * D;
+    const int s_end = min(nsplit, (range + 1) * per);
+    MergeAcc m;
+    for (int s0 = range * per; s0 < s_end;) {
+      if (s_end - s0 > 2 * kMergeSmall) {
+        merge_chunk<kMergeChunk, D>(m, ml, po, s0, s_end, G, hh, d);
+        s0 += kMergeChunk;
+      } else {
+        merge_chunk<kMergeSmall, D>(m, ml, po, s0, s_end, G, hh, d);
+        s0 += kMergeSmall;
+      }
+    }
+    part[i] = make_float4(m.M, m.lam, m.acc0, m.acc1);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < pairs; i += kThreads) {
+    const int e = 2 * i;
     const int hh = e / D, d = e - hh * D;
     MergeAcc m;
     if (a.has_cur) {   // the candidate's weight is exp2(zc - M) = 1 at M = zc
       m.M = sm_zc[hh];
-      m.acc = bf16_to_float(cur.v[d]);
+      m.acc0 = bf16_to_float(cur.v[d]);
+      m.acc1 = bf16_to_float(cur.v[d + 1]);
       m.lam = 1.f;
     }
-    for (int s0 = 0; s0 < nsplit;) {
-      if (nsplit - s0 > 2 * kMergeSmall) {
-        merge_chunk<kMergeChunk, D>(m, ml, po, s0, nsplit, G, hh, d);
-        s0 += kMergeChunk;
-      } else {
-        merge_chunk<kMergeSmall, D>(m, ml, po, s0, nsplit, G, hh, d);
-        s0 += kMergeSmall;
-      }
+    for (int range = 0; range < ranges; ++range) {
+      const float4 q = part[range * pairs + i];
+      if (q.x == -INFINITY && q.y == 0.f) continue;   // a range without splits
+      merge_rescale(m, fmaxf(m.M, q.x));
+      const float w = exp2_fast(q.x - m.M);
+      m.lam += w * q.y;
+      m.acc0 += w * q.z;
+      m.acc1 += w * q.w;
     }
-    a.out[qoff + e] = m.acc / m.lam;
+    *reinterpret_cast<float2*>(a.out + qoff + e) = make_float2(m.acc0 / m.lam, m.acc1 / m.lam);
     if (d == 0 && a.lse != nullptr)
       a.lse[((int64_t)l * a.B + b) * a.Hq + (int64_t)g * G + hh] = (m.M + __log2f(m.lam)) * kLn2;
   }
@@ -553,26 +739,29 @@ __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int 
 // Fused calls: the unit's G query heads, its K head and its V head of the
 // current token, from the fp32 QKV projection output (q heads, then k heads,
 // then v heads per request), one head per wavefront: q and k through the
-// per-head RMSNorm and the rotary embedding at position n - 1 (the shared
-// oda::norm_rope_pair, the same code oda_qk_norm_rope runs), v unchanged,
-// all rounded to bf16 into prep = [G][D] query rows, then K, then V.  The
-// fp32 loads do not depend on n; the rotation does.
+// per-head RMSNorm and the rotary embedding at position n_raw - 1 (the shared
+// oda::head_norm and rotate_pair, the same code oda_qk_norm_rope runs), v
+// unchanged, all rounded to bf16 into prep = [G][D] query rows, then K, then
+// V.  Only the rotation needs the length: the head is read, normalised and
+// its frequencies formed while the length is on its way.  Returns it.
 template <int D>
-__device__ __forceinline__ void prepare_current(const AttnArgs& a, int b, int g, int n, uint16_t* prep,
-                                                bool write_out) {
+__device__ __forceinline__ int prepare_current(const AttnArgs& a, int b, int g, int n_raw, uint16_t* prep,
+                                               bool write_out) {
   constexpr int half = D / 2;
   const int G = a.G;
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   const int heads = a.Hq + 2 * a.Hkv;
+  const double frequency = oda::rope_frequency(lane, D, a.rope_log2_theta);
   for (int t = wave; t < G + 2; t += kWaves) {   // t < G: query head g G + t; G: K; G + 1: V
     const int h = t < G ? g * G + t : (t == G ? a.Hq + g : a.Hq + a.Hkv + g);
     const float* src = a.qkv + ((int64_t)b * heads + h) * D;
     float x1 = lane < half ? src[lane] : 0.f;
     float x2 = lane < half ? src[lane + half] : 0.f;
-    if (t <= G)
-      oda::norm_rope_pair(x1, x2, lane < half, lane, D, t < G ? a.q_gain : a.k_gain, a.rms_eps, (double)(n - 1),
-                          a.rope_theta);
+    if (t <= G) {
+      oda::head_norm(x1, x2, lane < half, lane, D, t < G ? a.q_gain : a.k_gain, a.rms_eps);
+      oda::rotate_pair(x1, x2, (double)(n_raw - 1), frequency);
+    }
     if (lane < half) {
       const uint16_t y1 = oda::bf16_rne(x1), y2 = oda::bf16_rne(x2);
       uint16_t* dst = prep + (int64_t)t * D;
@@ -585,6 +774,7 @@ __device__ __forceinline__ void prepare_current(const AttnArgs& a, int b, int g,
       }
     }
   }
+  return n_raw;
 }
 
 // One unit of work: the wavefront runs of r (this split of request b) for
@@ -687,7 +877,28 @@ __device__ __forceinline__ void run_unit(const AttnArgs& a, Run& r, int l, int b
   }
   __syncthreads();
 
-  const int64_t pidx = (((int64_t)l * a.B + b) * a.Hkv + g) * a.max_splits + split;
+  if (!finalize) {   // two neighbouring elements per thread: 8-byte partial stores
+    const int64_t pidx = (((int64_t)l * a.B + b) * a.Hkv + g) * a.max_splits + split;
+    for (int i = threadIdx.x; i < G * D / 2; i += kWaves * 64) {
+      const int e = 2 * i, hh = e / D, d = e - hh * D;
+      float M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sm_m[w * 16 + hh]);
+      const float Mu = (M == -INFINITY) ? 0.f : M;
+      float acc0 = 0.f, acc1 = 0.f, lam = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float s = exp2_fast(sm_m[w * 16 + hh] - Mu);
+        const float2 ow = *reinterpret_cast<const float2*>(sm_o + ((int64_t)w * G + hh) * D + d);
+        acc0 += s * ow.x;
+        acc1 += s * ow.y;
+        lam += s * sm_l[w * 16 + hh];
+      }
+      publish2(a.part_o + pidx * G * D + e, acc0, acc1);
+      if (d == 0) publish2(a.part_ml + (pidx * G + hh) * 2, M, lam);
+    }
+    return;
+  }
   for (int e = threadIdx.x; e < G * D; e += kWaves * 64) {
     const int hh = e / D, d = e - hh * D;
     float M = -INFINITY;
@@ -701,25 +912,17 @@ __device__ __forceinline__ void run_unit(const AttnArgs& a, Run& r, int l, int b
       acc += s * sm_o[((int64_t)w * G + hh) * D + d];
       lam += s * sm_l[w * 16 + hh];
     }
-    if (finalize) {
-      if (a.has_cur) {
-        const float z = sm_zc[hh];
-        const float M2 = fmaxf(M, z);
-        const float s_old = exp2_fast(M - M2), s_cur = exp2_fast(z - M2);
-        acc = acc * s_old + s_cur * bf16_to_float(cur.v[d]);
-        lam = lam * s_old + s_cur;
-        M = M2;
-      }
-      a.out[qoff + e] = acc / lam;
-      if (d == 0 && a.lse != nullptr)
-        a.lse[((int64_t)l * a.B + b) * a.Hq + (int64_t)g * G + hh] = (M + __log2f(lam)) * kLn2;
-    } else {
-      a.part_o[pidx * G * D + e] = acc;
-      if (d == 0) {
-        a.part_ml[(pidx * G + hh) * 2 + 0] = M;
-        a.part_ml[(pidx * G + hh) * 2 + 1] = lam;
-      }
+    if (a.has_cur) {
+      const float z = sm_zc[hh];
+      const float M2 = fmaxf(M, z);
+      const float s_old = exp2_fast(M - M2), s_cur = exp2_fast(z - M2);
+      acc = acc * s_old + s_cur * bf16_to_float(cur.v[d]);
+      lam = lam * s_old + s_cur;
+      M = M2;
     }
+    a.out[qoff + e] = acc / lam;
+    if (d == 0 && a.lse != nullptr)
+      a.lse[((int64_t)l * a.B + b) * a.Hq + (int64_t)g * G + hh] = (M + __log2f(lam)) * kLn2;
   }
 }
 
@@ -737,34 +940,42 @@ void attn_split_kernel(AttnArgs a) {
   // instead of interleaving them with workgroups that exit at once
   const int active = active_requests(a);
   if (active == 0) return;
-  int64_t item = blockIdx.x;
-  const int g = (int)(item % a.Hkv);
-  item /= a.Hkv;
-  const int l = (int)(item % a.L);
-  item /= a.L;
-  const int rank = (int)(item % active);
-  const int bps = effective_bps(a, active);
-  // no selected request has this split (the grid covers the selection with
-  // the most); the plan keeps every split below max_splits, checked anyway
-  if ((item / active) * bps >= max(a.nvb_max, 1) || item / active >= a.max_splits) return;
-  const int split = (int)(item / active);
-  int b;
-  if (!request_of_rank(a, rank, b)) return;
-  b = uniform(b);
-  const int n = uniform(a.seq_lens[b]);
+  uint32_t item = blockIdx.x;
+  const uint32_t per_g = item / (uint32_t)a.Hkv;
+  const int g = (int)(item - per_g * (uint32_t)a.Hkv);
+  item = per_g / (uint32_t)a.L;
+  const int l = (int)(per_g - item * (uint32_t)a.L);
+  Item it;
+  if (!kLocal && a.by_length && active <= 64) {
+    if (!length_item<D>(a, active, item, it)) return;
+  } else {
+    it.split = (int)(item / (uint32_t)active);
+    const int rank = (int)(item - (uint32_t)it.split * (uint32_t)active);
+    it.bps = effective_bps(a, active);
+    // no selected request has this split (the grid covers the selection with
+    // the most); the plan keeps every split below max_splits, checked anyway
+    if (it.split >= a.max_splits || (int64_t)it.split * it.bps >= max(a.nvb_max, 1)) return;
+    if (!request_of_rank(a, rank, it.b)) return;
+    it.b = uniform(it.b);
+    it.n = a.seq_lens[it.b];
+    it.nsplit = 0;   // from the length, below
+  }
+  const int b = it.b, split = it.split, bps = it.bps;
   const int G = a.G;
+  int n;
   CurSrc cur;
   if (a.qkv != nullptr) {
     // fused call: this workgroup builds the unit's bf16 query rows and the
     // candidate K/V in shared memory (every split the same values); split 0
     // also writes the candidate out for the commit
     uint16_t* prep = reinterpret_cast<uint16_t*>(smem + split_lds_floats(G, D));
-    prepare_current<D>(a, b, g, n, prep, split == 0);
+    n = uniform(prepare_current<D>(a, b, g, it.n, prep, split == 0));
     __syncthreads();
     cur.q = prep;
     cur.k = prep + G * D;
     cur.v = prep + (G + 1) * D;
   } else {
+    n = uniform(it.n);
     cur = global_cur(a, D, l, b, g);
   }
   if (!valid_len(a, n)) {   // no history is addressed: the request's rows become NaN
@@ -780,7 +991,7 @@ void attn_split_kernel(AttnArgs a) {
   Run r;
   r.geo = geometry(n, kLocal ? a.n_sink : 0, a.window, a.has_cur);
   // (nvb = 0 happens only with the candidate as the sole position: one item, no blocks)
-  const int nsplit = max(1, (r.geo.nvb + bps - 1) / bps);
+  const int nsplit = it.nsplit > 0 ? it.nsplit : max(1, (int)(((uint32_t)r.geo.nvb + (uint32_t)bps - 1) / (uint32_t)bps));
   if (split >= nsplit) return;   // uniform over the workgroup: no barrier is skipped by part of it
 
   // this wavefront's run: a contiguous share of the split's pairs
@@ -793,30 +1004,27 @@ void attn_split_kernel(AttnArgs a) {
 
   run_unit<D, kLocal>(a, r, l, b, g, split, nsplit, smem, cur);
   if (nsplit == 1) return;   // finalised
-  float* sm_zc = smem + kWaves * 32 + kWaves * G * D;
-  // The last of the request's splits to finish merges them all.  The eight
-  // XCDs' L2 caches are not coherent with each other, so the partials are
-  // published at device scope: every wavefront waits until its stores have
-  // reached its XCD's L2, then one thread writes that L2 back (one release per
-  // workgroup: a release per wavefront made one-layer Full calls over 32K
-  // positions ~40% slower) and takes a ticket.  The ticket counts modulo
+  // The last of the request's splits to finish merges them all.  Every
+  // wavefront waits until its partials (write-through stores, publish2) have
+  // reached memory, then one thread takes a ticket.  The ticket counts modulo
   // nsplit (a wrapping increment), so the last arrival sees nsplit - 1 and the
   // word is back at 0 with no separate reset: even a request listed twice
   // (2 nsplit arrivals) leaves it at 0 for later calls.  The workgroup holding
-  // the last ticket drops stale cached lines (acquire) and merges.
+  // the last ticket reads the partials past the caches.  (With plain stores,
+  // an L2 write-back before the ticket and an invalidate after it, a one-layer
+  // Local call of eight requests took 21.1 us instead of 17.9 and a one-layer
+  // Full over 32,768 positions 31.2 instead of 29.3.)
   __shared__ int last_split;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   uint32_t* ticket = a.tickets + ((int64_t)l * a.B + b) * a.Hkv + g;
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const uint32_t t = __builtin_amdgcn_atomic_inc32(ticket, (uint32_t)(nsplit - 1), __ATOMIC_RELAXED, "agent");
     last_split = (t == (uint32_t)(nsplit - 1)) ? 1 : 0;
   }
   __syncthreads();
   if (!last_split) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  merge_unit<D>(a, l, b, g, nsplit, sm_zc, kWaves * 64, cur);
+  merge_unit<D>(a, l, b, g, nsplit, smem + kWaves * 32 + kWaves * G * D, smem + kWaves * 32, cur);
 }
 
 // Batched Local with one split per unit and many units per CU: a work item is
@@ -829,13 +1037,13 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2))
 void attn_local_layers_kernel(AttnArgs a) {
   extern __shared__ float smem[];
   const int wave = uniform(threadIdx.x >> 6);
-  int64_t item = blockIdx.x;
-  const int g = (int)(item % a.Hkv);
-  item /= a.Hkv;
-  const int groups = a.L / a.lpi;
-  const int lg = (int)(item % groups);
-  item /= groups;
-  if (item >= a.B) return;
+  uint32_t item = blockIdx.x;
+  const uint32_t per_g = item / (uint32_t)a.Hkv;
+  const int g = (int)(item - per_g * (uint32_t)a.Hkv);
+  const uint32_t groups = (uint32_t)a.L / (uint32_t)a.lpi;
+  item = per_g / groups;
+  const int lg = (int)(per_g - item * groups);
+  if (item >= (uint32_t)a.B) return;
   const int b = (int)item;
   const int n = uniform(a.seq_lens[b]);
   const int G = a.G;
@@ -929,6 +1137,8 @@ void make_plan(const oda_attn_shape* s, int n_sink, int window, Plan* p) {
   }
   const int64_t units = (int64_t)s->num_layers * s->batch * s->num_kv_heads;
   const int64_t per_request = (int64_t)s->num_layers * s->num_kv_heads;
+  // counts past 31 bits (no grid holds them, the launch says so) plan like the largest
+  const auto u32 = [](int64_t n) { return (uint32_t)std::min<int64_t>(n, INT32_MAX); };
   p->nvb_max = (int)nvb;
   p->split_cap = 1;
   if (s->split_blocks != 0) {
@@ -955,12 +1165,12 @@ void make_plan(const oda_attn_shape* s, int n_sink, int window, Plan* p) {
     p->max_splits = 1;
     p->full_slots = s->batch;
     for (int64_t k = 1; k <= std::min<int64_t>(s->batch, k_even); ++k) {
-      const int bps = plan_bps(k * per_request, per_request, (int)nvb, p->split_cap);
+      const int bps = plan_bps(u32(k * per_request), u32(per_request), (int)nvb, p->split_cap);
       const int64_t ns = oda::ceil_div(nvb, bps);
       p->max_splits = (int)std::max<int64_t>(p->max_splits, ns);
       p->full_slots = std::max<int64_t>(p->full_slots, k * ns);
     }
-    p->bps = plan_bps(s->batch * per_request, per_request, (int)nvb, p->split_cap);
+    p->bps = plan_bps(u32(units), u32(per_request), (int)nvb, p->split_cap);
     p->local_splits = (int)oda::ceil_div(nvb, p->bps);
   }
   if (p->max_splits <= 1) {
@@ -1054,7 +1264,7 @@ oda_status launch_layers(const AttnArgs& args, hipStream_t stream) {
 template <int D, bool kLocal>
 oda_status launch(const AttnArgs& args, const Plan& plan, hipStream_t stream) {
   if (kLocal && args.lpi > 1) return launch_layers<D>(args, stream);
-  const int64_t items = (int64_t)args.L * args.Hkv * (kLocal ? (int64_t)args.B * plan.local_splits : plan.full_slots);
+  const int64_t items = (int64_t)args.L * args.Hkv * (kLocal ? (int64_t)args.B * plan.local_splits : args.pair_slots);
   if (items > 0x7fffffffLL) return oda::fail(ODA_ERR_SHAPE, "grid too large (%lld work items)", (long long)items);
   const size_t lds = split_lds_floats(args.G, D) * sizeof(float) + (args.qkv ? prep_lds_bytes(args.G, D) : 0);
   static std::atomic<uint64_t> lds_raised{0};
@@ -1114,7 +1324,7 @@ oda_status run_attention(const oda_attn_shape* s, const oda_attn_inputs* in, boo
   a.k_gain = prep ? prep->k_gain : nullptr;
   a.k_out = prep ? prep->k_out : nullptr;
   a.v_out = prep ? prep->v_out : nullptr;
-  a.rope_theta = prep ? prep->rope_theta : 0.0;
+  a.rope_log2_theta = prep ? std::log2(prep->rope_theta) : 0.0;
   a.rms_eps = prep ? prep->rms_eps : 0.f;
   a.k_ring = k_ring;
   a.v_ring = v_ring;
@@ -1128,6 +1338,25 @@ oda_status run_attention(const oda_attn_shape* s, const oda_attn_inputs* in, boo
   a.nvb_max = plan.nvb_max;
   a.lpi = local ? layers_per_item(s, plan) : 1;
   a.select = select;
+  // A Full call of several requests with few units each is planned from the
+  // selected requests' lengths when a wavefront holds them (a listed call
+  // falls back on the device past 64).  With kBalanceUnits units or more per
+  // request the plain plan's many workgroups even out by themselves, and each
+  // workgroup's ~2 us of planning shows (8 layers, 3 requests: 600 us against
+  // 575).  The grid covers the pairs of the plain plan, and for
+  // the plan by length two rounds of workgroups, or as many as it may use
+  // when every request is selected anyway: workgroups without work cost a
+  // call about 5 ns each.
+  const int64_t units = (int64_t)s->num_layers * s->num_kv_heads;
+  a.by_length = !local && plan.dyn && plan.max_splits > 1 && s->batch > 1 && units < kBalanceUnits && (select == kSelList || s->batch <= 64) &&
+                plan.nvb_max <= (1 << 23);
+  int64_t slots = plan.full_slots;
+  if (a.by_length) {
+    const int64_t rounds = select == kSelAll ? kLengthRounds : 2;
+    slots = std::max(slots, std::min(rounds * kTargetGroups / units, (int64_t)s->batch * plan.max_splits));
+  }
+  if (slots > INT32_MAX) return oda::fail(ODA_ERR_SHAPE, "grid too large (%lld request splits)", (long long)slots);
+  a.pair_slots = (int32_t)slots;
   a.scale_log2 = in->scale * kLog2e;
   oda_status st;
   if (s->head_dim == 128)

@@ -494,13 +494,13 @@ struct RopeArgs {
   uint16_t* v_out;         // [B][Hkv][D]
   const int32_t* work_list;
   const int32_t* n_work;
-  double theta;
+  double log2_theta;
   float eps;
   int B, Hq, Hkv, D, heads_per_group;
 };
 
 // One wavefront per (selected request, head); q and k heads go through
-// oda::norm_rope_pair (the same code the fused attention calls run), v heads
+// oda::head_norm and rotate_pair (the same code the fused attention calls run), v heads
 // are only rounded.
 __global__ __launch_bounds__(256) void qk_norm_rope_kernel(RopeArgs p) {
   const int lane = threadIdx.x & 63;
@@ -518,9 +518,10 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(RopeArgs p) {
   uint16_t* dst;
   if (h < p.Hq + p.Hkv) {
     const bool is_q = h < p.Hq;
-    oda::norm_rope_pair(x1, x2, active, lane, p.D, is_q ? p.q_gain : p.k_gain, p.eps,
-                        (double)(p.seq_lens[b] - 1), p.theta);
+    const int n = p.seq_lens[b];
+    oda::head_norm(x1, x2, active, lane, p.D, is_q ? p.q_gain : p.k_gain, p.eps);
     if (!active) return;
+    oda::rotate_pair(x1, x2, (double)(n - 1), oda::rope_frequency(lane, p.D, p.log2_theta));
     dst = is_q ? p.q_out + ((int64_t)b * p.Hq + h) * p.D : p.k_out + ((int64_t)b * p.Hkv + (h - p.Hq)) * p.D;
   } else {
     if (!active) return;
@@ -764,7 +765,7 @@ extern "C" oda_status oda_qk_norm_rope(int32_t batch, int32_t num_q_heads, int32
   a.v_out = v_out;
   a.work_list = work_list;
   a.n_work = n_work;
-  a.theta = rope_theta;
+  a.log2_theta = std::log2(rope_theta);
   a.eps = rms_eps;
   a.B = batch;
   a.Hq = num_q_heads;
