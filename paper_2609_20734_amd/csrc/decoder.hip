@@ -601,58 +601,76 @@ __global__ __launch_bounds__(256) void rms_norm_rows_kernel(const float* x, cons
 constexpr int kArgThreads = 1024;
 
 // Greedy choice: the first index of the largest non-NaN value (-1 if every
-// value is NaN).  One workgroup per request, eight 16-byte loads in flight
-// per thread.
+// value is NaN).  One workgroup per request, bound by what one CU reads: the
+// values pass in groups of four, of which a thread keeps the best group's
+// maximum and number (five operations a group; tracking each value's index
+// took four times as many and, at 151,936 values, 16.7 us instead of 8.8).
+// The winning group is read again for the position.  kInFlight: 16-byte loads
+// in flight per thread (4 where one round of 4 covers the row).
+template <int kInFlight>
 __global__ __launch_bounds__(kArgThreads) void argmax_kernel(const float* x, int n, int32_t* index) {
   __shared__ float sv[kArgThreads / 64];
   __shared__ int si[kArgThreads / 64];
   const int b = blockIdx.x;
   const float* row = x + (int64_t)b * n;
+  const int n4 = n / 4;                        // the host keeps n a multiple of 4
   float best = -INFINITY;
-  int bidx = INT_MAX;
-  auto take = [&](float v, int i) {
-    if (v > best || (v == best && i < bidx)) {
-      best = v;
-      bidx = i;
-    }
-  };
-  const int n4 = n / 4;
-  for (int j0 = threadIdx.x; j0 < n4; j0 += kArgThreads * 8) {
-    float4 v[8];
+  int group = INT_MAX;
+  for (int j0 = threadIdx.x; j0 < n4; j0 += kArgThreads * kInFlight) {
+    float4 v[kInFlight];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u * kArgThreads;
-      v[u] = j < n4 ? *reinterpret_cast<const float4*>(row + 4 * (int64_t)j)
-                    : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    }
+    for (int u = 0; u < kInFlight; ++u)     // past the end: the last group again (not a new maximum)
+      v[u] = *reinterpret_cast<const float4*>(row + 4 * (int64_t)min(j0 + u * kArgThreads, n4 - 1));
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u * kArgThreads;
-      if (j < n4) {
-        take(v[u].x, 4 * j);
-        take(v[u].y, 4 * j + 1);
-        take(v[u].z, 4 * j + 2);
-        take(v[u].w, 4 * j + 3);
+    for (int u = 0; u < kInFlight; ++u) {
+      const float m = fmaxf(fmaxf(v[u].x, v[u].y), fmaxf(v[u].z, v[u].w));   // ignores NaNs
+      if (m > best) {                          // a thread's groups ascend: the first of equals stays
+        best = m;
+        group = min(j0 + u * kArgThreads, n4 - 1);
       }
     }
   }
-  for (int i = 4 * n4 + threadIdx.x; i < n; i += kArgThreads) take(row[i], i);
-  // wavefront, then workgroup
+  // wavefront, then workgroup: the largest value, of equals the first group
+  auto take = [&](float ov, int og) {
+    if (ov > best || (ov == best && og < group)) {
+      best = ov;
+      group = og;
+    }
+  };
 #pragma unroll
   for (int s = 32; s >= 1; s >>= 1) {
     const float ov = __shfl_xor(best, s);
-    const int oi = __shfl_xor(bidx, s);
-    take(ov, oi);
+    const int og = __shfl_xor(group, s);
+    take(ov, og);
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) {
     sv[wave] = best;
-    si[wave] = bidx;
+    si[wave] = group;
   }
   __syncthreads();
+  best = sv[0];
+  group = si[0];
+  for (int w = 1; w < kArgThreads / 64; ++w) take(sv[w], si[w]);
+  if (group != INT_MAX) {
+    if (threadIdx.x == 0) {
+      const float4 v = *reinterpret_cast<const float4*>(row + 4 * (int64_t)group);
+      index[b] = 4 * group + (v.x == best ? 0 : v.y == best ? 1 : v.z == best ? 2 : 3);
+    }
+    return;
+  }
+  // nothing above -infinity: the first value that is not NaN, if any
+  int first = INT_MAX;
+  for (int i = threadIdx.x; i < n && first == INT_MAX; i += kArgThreads)
+    if (row[i] == row[i]) first = i;
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) first = min(first, __shfl_xor(first, s));
+  __syncthreads();
+  if (lane == 0) si[wave] = first;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kArgThreads / 64; ++w) take(sv[w], si[w]);
-    index[b] = bidx == INT_MAX ? -1 : bidx;
+    for (int w = 1; w < kArgThreads / 64; ++w) first = min(first, si[w]);
+    index[b] = first == INT_MAX ? -1 : first;
   }
 }
 
@@ -826,6 +844,9 @@ extern "C" oda_status oda_argmax(int32_t batch, int32_t n, const float* x, int32
   if (batch < 1 || n < 1) return oda::fail(ODA_ERR_SHAPE, "batch and n must be >= 1");
   if (!oda::aligned(x, 16) || n % 4) return oda::fail(ODA_ERR_SHAPE, "x must be 16-byte aligned and n a multiple of 4");
   (void)hipGetLastError();
-  hipLaunchKernelGGL(argmax_kernel, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
+  if (n / 4 <= 4 * kArgThreads)
+    hipLaunchKernelGGL(argmax_kernel<4>, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
+  else
+    hipLaunchKernelGGL(argmax_kernel<16>, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
   return launch_status();
 }
