@@ -3,14 +3,15 @@
 // exceeds the threshold or is nonfinite), with on-device compaction of the
 // flagged requests.  No score is read by the host (App. A.5).
 //
-// fp32 weights and arithmetic (App. A.2).  Each dense layer is one launch of a
-// batched GEMV kernel: an item is a group of R output rows for a tile of up to
-// 8 requests; its rows are streamed with 16-byte loads, several 256-float
-// chunks in flight, and every input load serves all R rows (the weights are
-// read once per batch tile).  Long rows split K over the four wavefronts of a
-// workgroup, which combine their sums in LDS.  RMSNorm of a layer's input is
-// folded into the same pass (the sum of squares is accumulated next to the
-// dot products), so normalised inputs are never stored.
+// fp32 weights and arithmetic (App. A.2).  Each dense layer is one launch: on
+// the fp32 matrix cores for four requests or more (gate_tile_kernel, five for
+// the MLP head), else a GEMV kernel, an item of which is a group of R output
+// rows for all requests; its rows are streamed with 16-byte loads, several
+// 256-float chunks in flight, and every input load serves all R rows.  Long
+// rows split K over the four wavefronts of a workgroup, which combine their
+// sums in LDS.  RMSNorm of a layer's input is folded into the same pass (the
+// sum of squares is accumulated next to the dot products), so normalised
+// inputs are never stored.
 //
 // The layers of the head are dependent launches on one stream.  For one or
 // two requests with towers up to 512 wide, each residual SwiGLU block is a
@@ -35,10 +36,12 @@
 
 namespace {
 
-constexpr int kBatchTile = 8;     // requests per wavefront
+constexpr int kBatchTile = 4;     // requests of the vector kernels' tile
 constexpr int kWaves = 4;         // wavefronts per workgroup
+constexpr int kSmallBatch = 3;    // larger batches take the matrix-core tiles (gate_tile_kernel)
+constexpr int kSmallBatchMlp = 4; // (the MLP head's one long layer)
 
-enum Mode { kTower = 0, kMlpHidden = 1, kGateUp = 3, kDown = 4 };
+enum Mode { kTower = 0, kMlpHidden = 1, kFusion = 2, kGateUp = 3, kDown = 4 };
 
 struct LinArgs {
   const float* W;        // [rows][K] (kTower: tower 0's weight; the others follow at w_stride)
@@ -82,22 +85,22 @@ __device__ __forceinline__ float4 load4_or_zero(const float* p, const float* saf
 // for long rows, so that one launch has enough loads in flight to cover HBM
 // latency), and combine their sums through LDS.  S = 1: every wavefront of
 // the workgroup owns an item of its own.
-template <int MODE, int R, int S>
+template <int MODE, int R, int S, int BT>
 __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
   constexpr bool kNorm = (MODE == kTower || MODE == kGateUp);
   constexpr bool kTwo = (MODE == kGateUp);
-  constexpr int kAcc = R * kBatchTile;
+  constexpr int kAcc = R * BT;
   static_assert(S == 1 || S == kWaves, "K is split over all wavefronts or none");
-  __shared__ float sm[S > 1 ? kWaves : 1][S > 1 ? (kTwo ? 2 : 1) * kAcc + kBatchTile : 1];
+  __shared__ float sm[S > 1 ? kWaves : 1][S > 1 ? (kTwo ? 2 : 1) * kAcc + BT : 1];
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   const int item = S == 1 ? blockIdx.x * kWaves + wave : blockIdx.x;
   const int part = S == 1 ? 0 : wave;
   const int groups = p.rows / R;             // the host keeps rows (and dt) multiples of R
   const int rg = item % groups;
-  const int b0 = (item / groups) * kBatchTile;
+  const int b0 = (item / groups) * BT;
   if (b0 >= p.B) return;                     // uniform over the workgroup when S > 1
-  const int nb = min(kBatchTile, p.B - b0);
+  const int nb = min(BT, p.B - b0);
 
   const float* W = p.W;
   const float* bias = p.bias;
@@ -119,13 +122,13 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
   // after the reduction; clamped to a valid element for lanes without one
   float epi = 0.f;
   if (MODE != kGateUp) {
-    const int ej = min(lane / kBatchTile, R - 1), eb = b0 + min(lane % kBatchTile, nb - 1);
+    const int ej = min(lane / BT, R - 1), eb = b0 + min(lane % BT, nb - 1);
     epi = MODE == kDown ? p.aux[(int64_t)eb * p.rows + row0 + ej] : bias[row0 + ej];
   }
 
-  float acc[R][kBatchTile], acc2[kTwo ? R : 1][kBatchTile], ss[kBatchTile];
+  float acc[R][BT], acc2[kTwo ? R : 1][BT], ss[BT];
 #pragma unroll
-  for (int bi = 0; bi < kBatchTile; ++bi) {
+  for (int bi = 0; bi < BT; ++bi) {
     ss[bi] = 0.f;
 #pragma unroll
     for (int j = 0; j < R; ++j) acc[j][bi] = 0.f;
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
     float4 gk = make_float4(1.f, 1.f, 1.f, 1.f);
     if (kNorm) gk = *reinterpret_cast<const float4*>(gain + k);
 #pragma unroll
-    for (int bi = 0; bi < kBatchTile; ++bi) {
+    for (int bi = 0; bi < BT; ++bi) {
       if (bi < nb) {
         const float4 x = *reinterpret_cast<const float4*>(X + (int64_t)(b0 + bi) * p.K + k);
         if (kNorm) ss[bi] += dot4(x, x);
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
   // reduce over the wavefront; lane j * 8 + bi keeps row j, request bi
   float v = 0.f, v2 = 0.f, my_ss = 0.f;
 #pragma unroll
-  for (int bi = 0; bi < kBatchTile; ++bi) {
+  for (int bi = 0; bi < BT; ++bi) {
     if (bi < nb) {
       const float s = kNorm ? wave_sum(ss[bi]) : 0.f;
       if (kNorm && lane == bi) my_ss = s;
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
       for (int j = 0; j < R; ++j) {
         const float t = wave_sum(acc[j][bi]);
         const float t2 = kTwo ? wave_sum(acc2[j][bi]) : 0.f;
-        if (lane == j * kBatchTile + bi) {
+        if (lane == j * BT + bi) {
           v = t;
           v2 = t2;
         }
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
       sm[wave][lane] = v;
       if (kTwo) sm[wave][kAcc + lane] = v2;
     }
-    if (kNorm && lane < kBatchTile) sm[wave][(kTwo ? 2 : 1) * kAcc + lane] = my_ss;
+    if (kNorm && lane < BT) sm[wave][(kTwo ? 2 : 1) * kAcc + lane] = my_ss;
     __syncthreads();
     if (wave != 0) return;
     if (lane < kAcc) {
@@ -210,15 +213,15 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
       }
     }
     if (kNorm) {
-      const int bi = lane % kBatchTile;
+      const int bi = lane % BT;
       my_ss = sm[0][(kTwo ? 2 : 1) * kAcc + bi];
 #pragma unroll
       for (int w = 1; w < S; ++w) my_ss += sm[w][(kTwo ? 2 : 1) * kAcc + bi];
     }
   } else if (kNorm) {
-    my_ss = __shfl(my_ss, lane % kBatchTile);   // lane j * 8 + bi needs request bi's sum of squares
+    my_ss = __shfl(my_ss, lane % BT);   // lane j * 8 + bi needs request bi's sum of squares
   }
-  const int j = lane / kBatchTile, bi = lane % kBatchTile;
+  const int j = lane / BT, bi = lane % BT;
   if (lane >= kAcc || bi >= nb) return;
   const int b = b0 + bi;
   const int row = row0 + j;
@@ -306,6 +309,251 @@ __global__ __launch_bounds__(256) void gate_fusion_kernel(LinArgs p) {
   if (lane >= nb) return;
   const int b = b0 + lane;
   p.Y[(int64_t)b * p.rows + row] = 0.5f * (s3 + silu(mine + brow));
+}
+
+// ---------------------------------------------------------------------------
+// dense layers for four or more requests, on the matrix cores
+// ---------------------------------------------------------------------------
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTileWaves = 8;      // wavefronts per workgroup; they split K
+constexpr int kTileEdge = 16;      // rows and requests of one MFMA tile
+constexpr int kTileChunk = 32;     // elements of K a wavefront stages at a time
+constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
+
+// One dense layer (or the fusion layer) for a tile of output rows and
+// requests per workgroup on v_mfma_f32_16x16x4_f32: fp32 weights and inputs as
+// they are, W's rows as the A operand, requests as columns.  The eight
+// wavefronts split K into contiguous stretches and add their tiles through
+// LDS in wavefront order.  Each walks its stretch in chunks of 32 elements,
+// the next chunk's weights and inputs in flight: both are read as 128-byte
+// runs, eight rows per load, and turned into operands through the
+// wavefront's own part of LDS (reading operands straight from memory, 16 rows
+// of 64 bytes per load with neighbouring lanes on different rows, is bound by
+// the loads).  A step's products are summed by themselves, one instruction
+// per element of a lane's 16 bytes, before they join the total: with longer
+// chains the scores erred more than on the vector kernels (12 seeds, d = 8192,
+// dt = 512, 8 requests, against 64 bits: 2.1e-7, with this 1.9e-7, vector
+// 2.0e-7), at 3-5% less time.  What bounds it: at d = 4096, dt = 256 the chain
+// of seven launches (~4.5 us each) and, at 32 requests, the towers' inputs,
+// read again by every workgroup; 63.6 us on the vector kernels, 39 here.
+// K is `parts` runs of `len` elements (1 run; the fusion layer's interaction
+// vector has nine of dt, built from the tower outputs while staging).
+// kHalf: eight rows and eight requests per workgroup; tile rows and columns
+// 8..15 hold them again over the second half of the chunks (the off-diagonal
+// quadrants are not used), so that small layers reach more CUs.
+template <int MODE, bool kHalf>
+__global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
+  constexpr bool kNorm = (MODE == kTower || MODE == kGateUp);
+  constexpr int S = MODE == kGateUp ? 2 : 1;          // weight streams: gate and up
+  constexpr int kEdge = kHalf ? 8 : kTileEdge;
+  constexpr int kPitch = kTileChunk + 4;              // staged rows on different banks
+  constexpr int kStage = kTileEdge * kPitch;
+  __shared__ union {
+    float stage[kTileWaves][S + 1][kStage];
+    f32x4 acc[kTileWaves][S][64];
+  } sm;
+  __shared__ float sm_ss[kTileWaves][kTileEdge];
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform(threadIdx.x >> 6);
+  const int h = lane & 15, j = lane >> 4;
+  // the batch tiles of a row group run next to each other on one XCD
+  const int seg_rows = MODE == kTower ? p.dt : p.rows;                // rows of one weight matrix
+  const int seg_tiles = (seg_rows + kEdge - 1) / kEdge;
+  const int groups = seg_tiles * (MODE == kTower ? 3 : 1);
+  const int span = 8 * ((p.B + kEdge - 1) / kEdge);
+  const int rg = (int)(blockIdx.x / span) * 8 + (int)(blockIdx.x % 8);
+  const int b0 = (int)(blockIdx.x % span) / 8 * kEdge;
+  if (rg >= groups || b0 >= p.B) return;
+  const int nb = min(kEdge, p.B - b0);
+  const int tower = MODE == kTower ? rg / seg_tiles : 0;
+  const int row0 = (rg - tower * seg_tiles) * kEdge;
+  const int64_t seg = tower * p.w_stride;
+  const int len = MODE == kFusion ? p.dt : p.K;
+  const int cpp = (len + kTileChunk - 1) / kTileChunk;                // chunks per part
+  const int total = MODE == kFusion ? 9 * cpp : cpp;
+  const int span_c = kHalf ? (total + 1) / 2 : total;                 // chunks of the first half
+  const int per = (span_c + kTileWaves - 1) / kTileWaves;
+  const int c0 = min(span_c, wave * per), c1 = min(span_c, c0 + per);
+
+  // load i reads row (weights) and request (inputs) 8i + lane / 8, elements
+  // 4 (lane % 8) .. + 3 of the chunk (kHalf: row and request lane / 8, chunk
+  // of half i); rows and requests past the last repeat it and are not stored
+  const int r8 = lane >> 3, k8 = 4 * (lane & 7);
+  const float* wrow[S][2];
+  const float* xrow[2];
+  const float* X = MODE == kTower ? p.X[tower] : MODE == kFusion ? p.aux : p.X[0];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int v = kHalf ? r8 : 8 * i + r8;
+    const int row = min(row0 + v, seg_rows - 1);
+    wrow[0][i] = p.W + seg + (int64_t)row * p.K;
+    if (S == 2) wrow[S - 1][i] = p.W2 + (int64_t)row * p.K;
+    xrow[i] = X + (int64_t)(b0 + min(v, nb - 1)) * len;
+  }
+  const float* gain = kNorm ? p.gain + seg : nullptr;
+
+  // this thread's output: its bias or residual is read now
+  const int oe = threadIdx.x;
+  const int orow = row0 + oe % kEdge, ob = b0 + oe / kEdge;
+  const bool writes = oe < kEdge * kEdge && orow < seg_rows && ob < b0 + nb;
+  float epi = 0.f, s3 = 0.f;
+  if (writes) {
+    if (MODE == kDown) epi = p.aux[(int64_t)ob * p.rows + orow];
+    else if (MODE != kGateUp) epi = p.bias[seg + orow];
+    if (MODE == kFusion) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s3 += p.aux[((int64_t)q * p.B + ob) * p.dt + orow];
+    }
+  }
+
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[S], w[S][2], x[2], x2[2], g[2];
+  float ss[2] = {0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < S; ++s) acc[s] = zero;
+  // element of chunk c for load i within its part, and the part; past the end: not inside
+  auto place = [&](int c, int i, int& part, int& m) {
+    const int cc = kHalf && i == 1 ? c + span_c : c;
+    part = MODE == kFusion ? cc / cpp : 0;
+    m = (cc - part * cpp) * kTileChunk + k8;
+    return c < c1 && cc < total && m < len;
+  };
+  const int64_t plane = (int64_t)p.B * p.dt;          // one tower's outputs
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int part, m;
+      const bool in = place(c, i, part, m);
+      if (MODE == kFusion) {
+        // a, b, c, ab, |a - b|, ac, |a - c|, bc, |b - c|
+        const int q = in ? part : 0;
+        const int u = q < 3 ? q : q < 7 ? 0 : 1, v = q < 3 ? q : q < 5 ? 1 : 2;
+        x[i] = *reinterpret_cast<const f32x4*>(xrow[i] + u * plane + (in ? m : 0));
+        x2[i] = *reinterpret_cast<const f32x4*>(xrow[i] + v * plane + (in ? m : 0));
+      } else {
+        x[i] = *reinterpret_cast<const f32x4*>(xrow[i] + (in ? m : 0));
+      }
+      if (kNorm) g[i] = *reinterpret_cast<const f32x4*>(gain + (in ? m : 0));
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        w[s][i] = *reinterpret_cast<const f32x4*>(wrow[s][i] + (in ? part * len + m : 0));
+    }
+  };
+  float* const stage = &sm.stage[wave][0][0];
+  auto put = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int part, m;
+      const bool in = place(c, i, part, m);
+      f32x4 v = x[i];
+      if (MODE == kFusion && part >= 3) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (part & 1) ? v[e] * x2[i][e] : fabsf(v[e] - x2[i][e]);
+      }
+      if (!in) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (kNorm) {
+        ss[i] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] *= g[i][e];
+      }
+      const int at = (8 * i + r8) * kPitch + k8;
+      *reinterpret_cast<f32x4*>(stage + at) = v;
+#pragma unroll
+      for (int s = 0; s < S; ++s) *reinterpret_cast<f32x4*>(stage + (s + 1) * kStage + at) = w[s][i];
+    }
+  };
+  auto multiply = [&]() {
+    f32x4 sum[S][kTileChunk / 16];
+#pragma unroll
+    for (int q = 0; q < kTileChunk / 16; ++q) {
+      const int at = h * kPitch + 16 * q + 4 * j;
+      const f32x4 xv = *reinterpret_cast<const f32x4*>(stage + at);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const f32x4 wv = *reinterpret_cast<const f32x4*>(stage + (s + 1) * kStage + at);
+        f32x4 part[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], zero, 0, 0, 0);
+        sum[s][q] = (part[0] + part[1]) + (part[2] + part[3]);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) acc[s] += sum[s][0] + sum[s][1];
+  };
+  if (c0 < c1) {
+    load(c0);
+    for (int c = c0; c + 1 < c1; ++c) {
+      put(c);
+      load(c + 1);
+      multiply();
+    }
+    put(c1 - 1);
+    multiply();
+  }
+
+  // add the wavefronts' tiles in order
+  if (kNorm) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int s = 4; s >= 1; s >>= 1) ss[i] += __shfl_xor(ss[i], s);
+      if ((lane & 7) == 0) sm_ss[wave][8 * i + r8] = ss[i];
+    }
+  }
+  __syncthreads();   // the staged chunks are no longer read
+#pragma unroll
+  for (int s = 0; s < S; ++s) sm.acc[wave][s][lane] = acc[s];
+  __syncthreads();
+  if (!writes) return;
+  // the wavefronts' parts (of both halves) pairwise: a chain of sixteen
+  // additions at the size of the result would be the largest rounding error
+  constexpr int kParts = kTileWaves * (kHalf ? 2 : 1);
+  float pv[kParts], pv2[kParts], ps[kParts];
+#pragma unroll
+  for (int i = 0; i < kParts; ++i) {
+    const int wv = i % kTileWaves, half = i / kTileWaves;
+    const int hr = oe % kEdge + 8 * half, hc = oe / kEdge + 8 * half;
+    const int at = (hr / 4) * 16 + hc;                // the lane that holds rows 4j..4j+3 of the column
+    pv[i] = sm.acc[wv][0][at][hr % 4];
+    pv2[i] = S == 2 ? sm.acc[wv][S - 1][at][hr % 4] : 0.f;
+    ps[i] = kNorm ? sm_ss[wv][hc] : 0.f;
+  }
+#pragma unroll
+  for (int d = kParts / 2; d >= 1; d /= 2) {
+#pragma unroll
+    for (int i = 0; i < d; ++i) {
+      pv[i] += pv[i + d];
+      pv2[i] += pv2[i + d];
+      ps[i] += ps[i + d];
+    }
+  }
+  const float v = pv[0], v2 = pv2[0], sq = ps[0];
+  const float inv = kNorm ? rsqrtf(sq / (float)p.K + p.eps) : 1.f;
+  float* y = p.Y + ((int64_t)tower * p.B + ob) * seg_rows + orow;
+  if (MODE == kTower) *y = silu(v * inv + epi);
+  else if (MODE == kMlpHidden) *y = gelu(v + epi);
+  else if (MODE == kGateUp) *y = silu(v * inv) * (v2 * inv);
+  else if (MODE == kDown) *y = epi + v;
+  else *y = 0.5f * (s3 + silu(v + epi));   // kFusion
+}
+
+template <int MODE>
+void launch_tile(const LinArgs& a, hipStream_t stream) {
+  const int seg_rows = MODE == kTower ? a.dt : a.rows;
+  const auto groups = [&](int edge) {
+    return oda::ceil_div(seg_rows, edge) * (MODE == kTower ? 3 : 1) * oda::ceil_div(a.B, edge);
+  };
+  const auto grid = [&](int edge) {
+    const int64_t row_groups = oda::ceil_div(seg_rows, edge) * (MODE == kTower ? 3 : 1);
+    return dim3((unsigned)(oda::ceil_div(row_groups, 8) * 8 * oda::ceil_div(a.B, edge)));
+  };
+  const bool half = groups(8) <= 2 * kTargetGroups;
+  const dim3 block(kTileWaves * 64);
+  if (half) hipLaunchKernelGGL((gate_tile_kernel<MODE, true>), grid(8), block, 0, stream, a);
+  else hipLaunchKernelGGL((gate_tile_kernel<MODE, false>), grid(kTileEdge), block, 0, stream, a);
 }
 
 constexpr int kSplitMaxB = 2;         // batches up to this size may take the split-hidden blocks
@@ -663,34 +911,46 @@ oda_status check_gate(const oda_gate_desc* g) {
   return ODA_OK;
 }
 
-template <int MODE, int R, int S>
+template <int MODE, int R, int S, int BT = kBatchTile>
 void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
-  const int64_t items = (int64_t)(a.rows / R) * oda::ceil_div(a.B, kBatchTile);
+  const int64_t items = a.rows / R;   // B <= BT: one batch tile
   const int64_t groups = S == 1 ? oda::ceil_div(items, kWaves) : items;
-  hipLaunchKernelGGL((gate_linear_kernel<MODE, R, S>), dim3((unsigned)groups), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL((gate_linear_kernel<MODE, R, S, BT>), dim3((unsigned)groups), dim3(256), 0, stream, a);
 }
 
-// Launch shape of a dense layer.  K is split over the four wavefronts of a
-// workgroup when rows are long (K >= 4096), or when there are too few items
-// to occupy the chip (< 1024) and every wavefront still gets whole chunks.
-// With more than two requests per tile, R = 4 (else 2) rows share each input
-// load while that still leaves >= 512 workgroups.  With one or two, only the
-// tower layer groups rows (R = 2, down to 256 workgroups): its inputs are
-// d_model long, and re-reading them for every row cost more than the wider
-// items (the d = 8192 head took 56 instead of 63 µs at B = 2); in the other
-// layers grouping at small batches measured slower.
+// Launch shape of a dense layer.  Four requests or more (five for the MLP
+// head's layer) take the matrix-core tiles: a call of the App. A.2 head at d =
+// 4096, dt = 256 takes 34 us at 4-16 requests and 39 at 32, against 37 (4), 53
+// (8) and 64 (32) on the vector kernels, whose every few rows re-read all
+// requests' inputs (at 3: 34 against 32); the MLP head 12.3 against 12.9 at
+// 32, but 8.4 against 7.4 at 4.
+//
+// Smaller batches: K is split over the four wavefronts of a workgroup when
+// rows are long (K >= 4096), or when there are too few rows to occupy the chip
+// (< 1024) and every wavefront still gets whole chunks.  With more than two
+// requests, R = 4 (else 2) rows share each input load while that still leaves
+// >= 512 workgroups.  With one or two, only the tower layer groups rows (R =
+// 2, down to 256 workgroups): its inputs are d_model long, and re-reading them
+// for every row cost more than the wider items (the d = 8192 head took 56
+// instead of 63 us at two requests); in the other layers grouping at small
+// batches measured slower.
 template <int MODE>
 void launch_linear(const LinArgs& a, hipStream_t stream) {
-  const int tiles = (int)oda::ceil_div(a.B, kBatchTile);
-  const int per_tile = std::min(a.B, kBatchTile);
-  const int unit = MODE == kTower ? a.dt : a.rows;   // R must divide it
-  const int64_t items = (int64_t)a.rows * tiles;
+  if constexpr (MODE == kMlpHidden) {
+    // a long and wide layer of up to eight requests streams faster from
+    // 16-byte row loads: 5716 -> 928 of five 14.2 us against 15.8
+    if (a.B > kSmallBatchMlp && a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20))
+      return a.rows % 2 == 0 && a.rows >= 1024 ? launch_linear_rs<MODE, 2, kWaves, 8>(a, stream)
+                                               : launch_linear_rs<MODE, 1, kWaves, 8>(a, stream);
+  }
+  if (a.B > (MODE == kMlpHidden ? kSmallBatchMlp : kSmallBatch)) return launch_tile<MODE>(a, stream);
+  const int64_t items = a.rows;
   const bool split = a.K >= 4096 || (a.K >= 1024 && items < 1024);
   auto fits = [&](int r) {
-    if (unit % r != 0) return false;
+    if ((MODE == kTower ? a.dt : a.rows) % r != 0) return false;   // R must divide it
     const int64_t groups = items / r / (split ? 1 : kWaves);
     if (MODE == kTower && r == 2 && groups >= 256) return true;
-    return per_tile > 2 && groups >= 512;
+    return a.B > 2 && groups >= 512;
   };
   if (split) {
     if (fits(4)) return launch_linear_rs<MODE, 4, kWaves>(a, stream);
@@ -705,6 +965,7 @@ void launch_linear(const LinArgs& a, hipStream_t stream) {
 // Fusion launch: S wavefronts per item when the tower width allows S steps
 // of 256 and the items alone would leave the chip under-occupied.
 void launch_fusion(const LinArgs& a, hipStream_t stream) {
+  if (a.B > kSmallBatch) return launch_tile<kFusion>(a, stream);
   const int64_t items = (int64_t)a.rows * oda::ceil_div(a.B, kBatchTile);
   const int steps = (int)oda::ceil_div(a.dt, 256);
   const int s = items >= 2048 ? 1 : steps >= 4 ? 4 : steps >= 2 ? 2 : 1;

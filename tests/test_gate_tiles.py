@@ -1,0 +1,43 @@
+"""The recall head for batches on the matrix-core tiles: request counts around
+the vector kernels' limits, 8 and 16, tower widths around 8, 16 and the
+32-element chunks, K shorter than a chunk and ragged over the wavefronts and
+halves, and nonfinite inputs staying in their request.
+
+Tolerance: scores are held to 4e-6 of the score scale.  A layer's fp32 sums of
+up to 8192 terms of random sign err by about 2e-7 of their size (chains of at
+most four, 32 and four additions), and the five layers' errors add."""
+import numpy as np
+import pytest
+
+import oda_synth as S
+from test_gate_parity import Gate, _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind,d,dh,B", [
+    ("paper", 4, 4, 4), ("paper", 100, 64, 3), ("paper", 36, 12, 8), ("paper", 68, 20, 9), ("paper", 516, 36, 16), ("paper", 1028, 124, 17),
+    ("paper", 2052, 260, 33), ("paper", 264, 1028, 4), ("paper", 4096, 132, 65), ("mlp", 4, 4, 5), ("mlp", 100, 28, 8),
+    ("mlp", 1020, 2052, 6), ("mlp", 8192, 516, 17), ("mlp", 8192, 516, 7),
+    ("mlp", 4100, 1026 * 2, 8)])
+def test_tile_edges(kind, d, dh, B):
+    gate = Gate(kind, d, dh, B, seed=d + dh)
+    h, e, l = (x[0] for x in S.gate_inputs(d + B, 1, B, d))
+    ref = gate.oracle(h.astype(np.float64), e.astype(np.float64), l.astype(np.float64))
+    sc, _, _ = _check(gate, h, e, l, float(np.median(ref)) + 0.01)
+    assert np.abs(sc - ref).max() <= 4e-6 * max(1.0, float(np.abs(ref).max()))
+
+
+@pytest.mark.parametrize("kind,B", [("paper", 5), ("paper", 18), ("mlp", 9)])
+def test_nonfinite_inputs_stay_in_their_request(kind, B):
+    d, dh = 264, 40
+    gate = Gate(kind, d, dh, B)
+    h, e, l = (x[0].copy() for x in S.gate_inputs(3, 1, B, d))
+    clean = gate.run(h, e, l, 1e9)[0]
+    l[1, 7] = np.nan
+    l[2, 100] = np.inf
+    sc, fl, wl, n = gate.run(h, e, l, 1e9)
+    assert not np.isfinite(sc[1]) and fl[1] == 1
+    assert kind == "mlp" or (not np.isfinite(sc[2]) and fl[2] == 1)   # inf / inf in the norm
+    keep = [b for b in range(B) if b not in (1, 2)]
+    assert np.array_equal(sc[keep], clean[keep]) and not fl[keep].any()
