@@ -333,13 +333,17 @@ constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
 // of 64 bytes per load with neighbouring lanes on different rows, is bound by
 // the loads).  A step's products are summed by themselves, one instruction
 // per element of a lane's 16 bytes, before they join the total: with longer
-// chains the scores erred more than on the vector kernels (12 seeds, d = 8192,
-// dt = 512, 8 requests, against 64 bits: 2.1e-7, with this 1.9e-7, vector
-// 2.0e-7), at 3-5% less time.  What bounds it: at d = 4096, dt = 256 the chain
-// of seven launches (~4.5 us each) and, at 32 requests, the towers' inputs,
-// read again by every workgroup; 63.6 us on the vector kernels, 39 here.
-// K is `parts` runs of `len` elements (1 run; the fusion layer's interaction
-// vector has nine of dt, built from the tower outputs while staging).
+// chains (3-5% faster) the scores erred more than on the vector kernels, with
+// these as much (40 seeds against 64 bits, 4096 / 256 / 32 requests 1.64e-7 and
+// 1.65e-7, 8192 / 512 / 8 1.76e-7 and 1.69e-7, 2048 / 1024 / 8 1.88e-7 and
+// 2.10e-7).  What bounds it: at d = 4096, dt = 256 the chain of seven launches
+// (~4.5 us each) and, at 32 requests, the towers' inputs, read again by every
+// workgroup; 63.6 us on the vector kernels, 37.0 here.
+// The fusion layer's K is nine runs of dt elements, a, b, c, ab, |a - b|, ac,
+// |a - c|, bc, |b - c|, built from the tower outputs while staging: a chunk
+// covers one tower's run and the two it forms with the next tower, so that two
+// input loads serve three of weights (run by run, with two input loads each,
+// the layer took 28.3 us at dt = 1024, 8 requests, instead of 17.2).
 // kHalf: eight rows and eight requests per workgroup; tile rows and columns
 // 8..15 hold them again over the second half of the chunks (the off-diagonal
 // quadrants are not used), so that small layers reach more CUs.
@@ -347,11 +351,12 @@ template <int MODE, bool kHalf>
 __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
   constexpr bool kNorm = (MODE == kTower || MODE == kGateUp);
   constexpr int S = MODE == kGateUp ? 2 : 1;          // weight streams: gate and up
+  constexpr int NT = MODE == kFusion ? 3 : 1;         // terms (weight run, input) of a chunk
   constexpr int kEdge = kHalf ? 8 : kTileEdge;
   constexpr int kPitch = kTileChunk + 4;              // staged rows on different banks
   constexpr int kStage = kTileEdge * kPitch;
   __shared__ union {
-    float stage[kTileWaves][S + 1][kStage];
+    float stage[kTileWaves][NT * (S + 1)][kStage];
     f32x4 acc[kTileWaves][S][64];
   } sm;
   __shared__ float sm_ss[kTileWaves][kTileEdge];
@@ -371,8 +376,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
   const int row0 = (rg - tower * seg_tiles) * kEdge;
   const int64_t seg = tower * p.w_stride;
   const int len = MODE == kFusion ? p.dt : p.K;
-  const int cpp = (len + kTileChunk - 1) / kTileChunk;                // chunks per part
-  const int total = MODE == kFusion ? 9 * cpp : cpp;
+  const int cpp = (len + kTileChunk - 1) / kTileChunk;                // chunks per run
+  const int total = NT * cpp;
   const int span_c = kHalf ? (total + 1) / 2 : total;                 // chunks of the first half
   const int per = (span_c + kTileWaves - 1) / kTileWaves;
   const int c0 = min(span_c, wave * per), c1 = min(span_c, c0 + per);
@@ -409,79 +414,93 @@ __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
   }
 
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[S], w[S][2], x[2], x2[2], g[2];
+  f32x4 acc[S], w[S * NT][2], x[2], x2[2], g[2];
   float ss[2] = {0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < S; ++s) acc[s] = zero;
-  // element of chunk c for load i within its part, and the part; past the end: not inside
-  auto place = [&](int c, int i, int& part, int& m) {
+  // element of chunk c for load i within its run, and (fusion) the tower; past the end: not inside
+  auto place = [&](int c, int i, int& q, int& m) {
     const int cc = kHalf && i == 1 ? c + span_c : c;
-    part = MODE == kFusion ? cc / cpp : 0;
-    m = (cc - part * cpp) * kTileChunk + k8;
+    q = MODE == kFusion ? cc / cpp : 0;
+    m = (cc - q * cpp) * kTileChunk + k8;
     return c < c1 && cc < total && m < len;
   };
   const int64_t plane = (int64_t)p.B * p.dt;          // one tower's outputs
   auto load = [&](int c) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      int part, m;
-      const bool in = place(c, i, part, m);
-      if (MODE == kFusion) {
-        // a, b, c, ab, |a - b|, ac, |a - c|, bc, |b - c|
-        const int q = in ? part : 0;
-        const int u = q < 3 ? q : q < 7 ? 0 : 1, v = q < 3 ? q : q < 5 ? 1 : 2;
-        x[i] = *reinterpret_cast<const f32x4*>(xrow[i] + u * plane + (in ? m : 0));
-        x2[i] = *reinterpret_cast<const f32x4*>(xrow[i] + v * plane + (in ? m : 0));
-      } else {
-        x[i] = *reinterpret_cast<const f32x4*>(xrow[i] + (in ? m : 0));
-      }
-      if (kNorm) g[i] = *reinterpret_cast<const f32x4*>(gain + (in ? m : 0));
+      int q, m;
+      const bool in = place(c, i, q, m);
+      m = in ? m : 0;
+      q = in ? q : 0;
+      x[i] = *reinterpret_cast<const f32x4*>(xrow[i] + (MODE == kFusion ? q * plane : 0) + m);
+      if (MODE == kFusion) x2[i] = *reinterpret_cast<const f32x4*>(xrow[i] + (q == 2 ? 0 : q + 1) * plane + m);
+      if (kNorm) g[i] = *reinterpret_cast<const f32x4*>(gain + m);
 #pragma unroll
-      for (int s = 0; s < S; ++s)
-        w[s][i] = *reinterpret_cast<const f32x4*>(wrow[s][i] + (in ? part * len + m : 0));
+      for (int t = 0; t < NT; ++t) {
+        // the tower's own run, its product (3, 7, 5) and its difference (4, 8, 6) with the next tower
+        const int run = t == 0 ? q : (q == 0 ? 2 : q == 1 ? 6 : 4) + t;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          w[t * S + s][i] = *reinterpret_cast<const f32x4*>(wrow[s][i] + (int64_t)run * len + m);
+      }
     }
   };
   float* const stage = &sm.stage[wave][0][0];
   auto put = [&](int c) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      int part, m;
-      const bool in = place(c, i, part, m);
-      f32x4 v = x[i];
-      if (MODE == kFusion && part >= 3) {
+      int q, m;
+      const bool in = place(c, i, q, m);
+      f32x4 v[NT];
+      v[0] = in ? x[i] : zero;
+      if (MODE == kFusion) {
+        const f32x4 y = in ? x2[i] : zero;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (part & 1) ? v[e] * x2[i][e] : fabsf(v[e] - x2[i][e]);
+        for (int e = 0; e < 4; ++e) {
+          v[NT / 2][e] = v[0][e] * y[e];
+          v[NT - 1][e] = fabsf(v[0][e] - y[e]);
+        }
       }
-      if (!in) v = f32x4{0.f, 0.f, 0.f, 0.f};
       if (kNorm) {
-        ss[i] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+        ss[i] += v[0][0] * v[0][0] + v[0][1] * v[0][1] + v[0][2] * v[0][2] + v[0][3] * v[0][3];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] *= g[i][e];
+        for (int e = 0; e < 4; ++e) v[0][e] *= g[i][e];
       }
       const int at = (8 * i + r8) * kPitch + k8;
-      *reinterpret_cast<f32x4*>(stage + at) = v;
 #pragma unroll
-      for (int s = 0; s < S; ++s) *reinterpret_cast<f32x4*>(stage + (s + 1) * kStage + at) = w[s][i];
+      for (int t = 0; t < NT; ++t) {
+        *reinterpret_cast<f32x4*>(stage + t * (S + 1) * kStage + at) = v[t];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          *reinterpret_cast<f32x4*>(stage + (t * (S + 1) + s + 1) * kStage + at) = w[t * S + s][i];
+      }
     }
   };
   auto multiply = [&]() {
-    f32x4 sum[S][kTileChunk / 16];
+    f32x4 term[NT][S];
 #pragma unroll
-    for (int q = 0; q < kTileChunk / 16; ++q) {
-      const int at = h * kPitch + 16 * q + 4 * j;
-      const f32x4 xv = *reinterpret_cast<const f32x4*>(stage + at);
+    for (int t = 0; t < NT; ++t) {
+      const float* const tile = stage + t * (S + 1) * kStage;
+      f32x4 sum[S][kTileChunk / 16];
 #pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const f32x4 wv = *reinterpret_cast<const f32x4*>(stage + (s + 1) * kStage + at);
-        f32x4 part[4];
+      for (int q = 0; q < kTileChunk / 16; ++q) {
+        const int at = h * kPitch + 16 * q + 4 * j;
+        const f32x4 xv = *reinterpret_cast<const f32x4*>(tile + at);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], zero, 0, 0, 0);
-        sum[s][q] = (part[0] + part[1]) + (part[2] + part[3]);
+        for (int s = 0; s < S; ++s) {
+          const f32x4 wv = *reinterpret_cast<const f32x4*>(tile + (s + 1) * kStage + at);
+          f32x4 part[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], zero, 0, 0, 0);
+          sum[s][q] = (part[0] + part[1]) + (part[2] + part[3]);
+        }
       }
+#pragma unroll
+      for (int s = 0; s < S; ++s) term[t][s] = sum[s][0] + sum[s][1];
     }
 #pragma unroll
-    for (int s = 0; s < S; ++s) acc[s] += sum[s][0] + sum[s][1];
+    for (int s = 0; s < S; ++s) acc[s] += NT == 3 ? term[0][s] + (term[NT / 2][s] + term[NT - 1][s]) : term[0][s];
   };
   if (c0 < c1) {
     load(c0);
@@ -920,10 +939,10 @@ void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
 
 // Launch shape of a dense layer.  Four requests or more (five for the MLP
 // head's layer) take the matrix-core tiles: a call of the App. A.2 head at d =
-// 4096, dt = 256 takes 34 us at 4-16 requests and 39 at 32, against 37 (4), 53
+// 4096, dt = 256 takes 32 us at 4-16 requests and 37 at 32, against 37 (4), 53
 // (8) and 64 (32) on the vector kernels, whose every few rows re-read all
-// requests' inputs (at 3: 34 against 32); the MLP head 12.3 against 12.9 at
-// 32, but 8.4 against 7.4 at 4.
+// requests' inputs (the d = 4328, dt = 436 head of 3: 42 against 39); the MLP
+// head 12.2 against 12.9 at 32, but 8.4 against 7.4 at 4.
 //
 // Smaller batches: K is split over the four wavefronts of a workgroup when
 // rows are long (K >= 4096), or when there are too few rows to occupy the chip
