@@ -615,11 +615,14 @@ __device__ __forceinline__ float2 published2(const float* p) {
 
 // Running state of two neighbouring output elements of the split merge:
 // maximum logit M (log2 units), weighted sums of partial outputs and of
-// partial denominators.
+// partial denominators.  M = -infinity (no splits yet, or splits whose logits
+// are all -infinity: M = -infinity, lam = 0) weighs nothing: weights are taken
+// against merge_base, so that -infinity - -infinity never arises.
 struct MergeAcc {
   float M = -INFINITY, lam = 0.f, acc0 = 0.f, acc1 = 0.f;
 };
 
+__device__ __forceinline__ float merge_base(float M) { return M == -INFINITY ? 0.f : M; }
 __device__ __forceinline__ void merge_rescale(MergeAcc& m, float M) {
   const float r = (M == m.M) ? 1.f : exp2_fast(m.M - M);
   m.acc0 *= r;
@@ -645,9 +648,10 @@ __device__ __forceinline__ void merge_chunk(MergeAcc& m, const float* ml, const 
 #pragma unroll
   for (int k = 0; k < C; ++k) Mc = fmaxf(Mc, mlv[k].x);
   merge_rescale(m, Mc);
+  const float Mu = merge_base(Mc);
 #pragma unroll
   for (int k = 0; k < C; ++k) {
-    const float w = (s0 + k < s_end) ? exp2_fast(mlv[k].x - Mc) : 0.f;
+    const float w = (s0 + k < s_end) ? exp2_fast(mlv[k].x - Mu) : 0.f;
     m.acc0 += w * ov[k].x;
     m.acc1 += w * ov[k].y;
     m.lam += w * mlv[k].y;
@@ -715,17 +719,16 @@ __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int 
     const int e = 2 * i;
     const int hh = e / D, d = e - hh * D;
     MergeAcc m;
-    if (a.has_cur) {   // the candidate's weight is exp2(zc - M) = 1 at M = zc
+    if (a.has_cur && sm_zc[hh] != -INFINITY) {   // the candidate's weight is exp2(zc - M) = 1 at M = zc
       m.M = sm_zc[hh];
       m.acc0 = bf16_to_float(cur.v[d]);
       m.acc1 = bf16_to_float(cur.v[d + 1]);
       m.lam = 1.f;
     }
-    for (int range = 0; range < ranges; ++range) {
+    for (int range = 0; range < ranges; ++range) {   // (the last may hold no splits)
       const float4 q = part[range * pairs + i];
-      if (q.x == -INFINITY && q.y == 0.f) continue;   // a range without splits
       merge_rescale(m, fmaxf(m.M, q.x));
-      const float w = exp2_fast(q.x - m.M);
+      const float w = exp2_fast(q.x - merge_base(m.M));
       m.lam += w * q.y;
       m.acc0 += w * q.z;
       m.acc1 += w * q.w;
