@@ -188,9 +188,10 @@ constexpr int kChunk = 64;         // elements of K a wavefront stages at a time
 constexpr int kMfmaMaxK = 1 << 28; // a tile's sixteen rows stay within 32-bit element offsets
 constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
 
-// x = p[0] + p[1] + p[2] with bf16 pieces, exactly: each piece is the leading
-// eight significant bits of what the ones before it leave (truncation, so no
-// piece overflows).  An infinity is its own first piece; a NaN stays one.
+// x = p[0] + p[1] + p[2] with bf16 pieces, exactly where the last piece is no
+// subnormal (|x| from 2^-110): each piece is the leading eight significant bits
+// of what the ones before it leave (truncation, so no piece overflows).  An
+// infinity is its own first piece, and so is a quiet NaN.
 __device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&p)[3]) {
   float r[8];
   float mx = 0.f;
@@ -344,10 +345,10 @@ void dense_mfma_kernel(DenseArgs p) {
 #pragma unroll
   for (int m = 0; m < kPairs; ++m) ss[m] = 0.f;
   u32x4 w[S][kWLoads];
-  f32x4 x[kPairs], g[kHalf ? 2 : 1];
+  f32x4 x[kPairs], g[kHalf ? 2 : 1] = {};
   const int kx = step0 * 32 + 4 * (lane % kLanes);                                // of chunk 0, within a half
   const int kw = step0 * 32 + 8 * (lane % kWLanes);
-  // an element past the end reads the row's start; its inputs count as zero
+  // an element past the end reads the row's start and counts as zero
   auto back_x = [&](int m) { return kHalf && m >= kPairs / 2 ? -khalf : 0; };
   auto load_x = [&](int c) {
 #pragma unroll
@@ -374,24 +375,32 @@ void dense_mfma_kernel(DenseArgs p) {
     }
   };
   float (&stage)[kMfmaRows][kPitch] = sm.x[wave];
-  auto put_x = [&](int c) {
+  // Only a stretch's last chunk can reach past its end: there inputs, gains and
+  // weights are zeroed, all of them, since 0 times an infinity would be NaN.
+  auto put_x = [&](int c, bool last) {
 #pragma unroll
     for (int m = 0; m < kPairs; ++m) {
-      f32x4 v = x[m];
-      if (kx + c * kChunk >= (kHalf && m >= kPairs / 2 ? stop1 : stop0)) v = f32x4{0.f, 0.f, 0.f, 0.f};
+      f32x4 v = x[m], gk = g[kHalf && m >= kPairs / 2 ? 1 : 0];
+      if (last && kx + c * kChunk >= (kHalf && m >= kPairs / 2 ? stop1 : stop0)) v = gk = f32x4{0.f, 0.f, 0.f, 0.f};
       if (kNorm) {
         ss[m] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-        const f32x4 gk = g[kHalf && m >= kPairs / 2 ? 1 : 0];
         v = f32x4{v[0] * gk[0], v[1] * gk[1], v[2] * gk[2], v[3] * gk[3]};
+      } else {   // NaNs quiet (the product does so above): truncated to bf16 they stay NaNs
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __builtin_canonicalizef(v[e]);
       }
       *reinterpret_cast<f32x4*>(&stage[kRowsAt * m + lane / kLanes][4 * (lane % kLanes)]) = v;
     }
   };
-  auto put_w = [&]() {
+  auto put_w = [&](int c, bool last) {
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
+    for (int i = 0; i < kWLoads; ++i) {
+      if (last && kw + c * kChunk >= (kHalf && i == 1 ? stop1 : stop0)) {
 #pragma unroll
-      for (int i = 0; i < kWLoads; ++i)
+        for (int s = 0; s < S; ++s) w[s][i] = u32x4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int s = 0; s < S; ++s)
         *reinterpret_cast<u32x4*>(&sm.w[wave][s][kMfmaRows / kWLoads * i + lane / kWLanes][8 * (lane % kWLanes)]) = w[s][i];
     }
   };
@@ -418,15 +427,15 @@ void dense_mfma_kernel(DenseArgs p) {
     load_x(0);
     load_w(0);
     for (int c = 0; c + 1 < chunks; ++c) {
-      put_x(c);
+      put_x(c, false);
       load_x(c + 1);
-      put_w();
+      put_w(c, false);
       load_w(c + 1);
 #pragma unroll
       for (int u = 0; u < U; ++u) step(u);
     }
-    put_x(chunks - 1);
-    put_w();
+    put_x(chunks - 1, true);
+    put_w(chunks - 1, true);
 #pragma unroll
     for (int u = 0; u < U; ++u) step(u);
   }
@@ -442,7 +451,14 @@ void dense_mfma_kernel(DenseArgs p) {
   }
   __syncthreads();   // the staged chunks are no longer read
 #pragma unroll
-  for (int s = 0; s < S; ++s) sm.acc[wave][s][lane] = acc[s] + low[s];
+  for (int s = 0; s < S; ++s) {
+    // an infinite weight makes `low` NaN where an input's lower pieces are
+    // zero: a sum of the leading pieces that is not finite is the result
+    f32x4 t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = fabsf(acc[s][i]) < INFINITY ? acc[s][i] + low[s][i] : acc[s][i];
+    sm.acc[wave][s][lane] = t;
+  }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {

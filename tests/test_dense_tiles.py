@@ -105,3 +105,40 @@ def test_nonfinite_inputs_stay_in_their_request(B):
         big = np.finfo(np.float32).max
         assert np.array_equal(got[2], np.where(np.arange(N) % 2 == 0, np.float32(0.5) * big, np.float32(-0.25) * big))
     assert np.array_equal(got[3:], clean[3:])
+
+
+@pytest.mark.parametrize("B,N", [(2, 24), (9, 24), (17, 5000), (1, 65552)])
+@pytest.mark.parametrize("K", [8, 136, 544, 1536])
+def test_infinite_weights_and_gains(K, N, B):
+    """A row with an infinite weight gives the infinity (or NaN) that a sum of
+    its products gives, wherever in K it lies (the stretch padding repeats a
+    row's first elements), whatever the lower bf16 pieces of the inputs; an
+    infinite gain alike; a NaN with only low payload bits stays a NaN."""
+    P = need_gpu()
+    g, W, x = _inputs(K + N + B, K, N, B)
+    x = np.abs(x) + 0.5
+    x[:, ::3] = 1.0                                        # its lower pieces are zero
+    inf, ninf = (int(S.f32_to_bf16_bits(np.full(1, v, np.float32))[0]) for v in (np.inf, -np.inf))
+    W[1, 0], W[2, K - 1], W[3, K // 2], W[4, 0], W[4, K - 2] = inf, ninf, inf, inf, ninf
+    rows = {1: np.inf, 2: -np.inf, 3: np.inf, 4: np.nan}
+    clean = np.setdiff1d(np.arange(N), list(rows))
+    gain = np.ones(K, np.float32)
+
+    def run(x, gain):
+        y = torch.empty(B, N, device="cuda")
+        P.dense_bf16(P.dense_desc(K, N, P.DENSE_PLAIN, dev_u16(W), dev_f32(gain) if gain is not None else None, 1e-6), B,
+                     dev_f32(x), None, y)
+        torch.cuda.synchronize()
+        return y.cpu().numpy()
+
+    for y in (run(x, None), run(x, gain)):
+        for r, v in rows.items():
+            assert np.array_equal(y[:, r], np.full(B, v, np.float32), equal_nan=True), (r, y[:, r])
+        assert np.all(np.isfinite(y[:, clean]))
+    gain[K - 1] = np.inf
+    want = np.where(OA.bf16_to_f64(W[:, K - 1]) > 0, np.inf, -np.inf)
+    some = clean[OA.bf16_to_f64(W[clean, K - 1]) != 0]
+    assert np.array_equal(run(x, gain)[:, some], np.tile(want[some], (B, 1)))
+    x[B - 1, K - 1] = np.array([0x7f800001], np.uint32).view(np.float32)[0]
+    y = run(x, None)
+    assert np.all(np.isnan(y[B - 1])) and np.all(np.isfinite(y[:B - 1][:, clean]))
