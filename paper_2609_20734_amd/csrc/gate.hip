@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
   }
 
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[S], w[S * NT][2], x[2], x2[2], g[2];
+  f32x4 acc[S], w[S * NT][2], x[2], x2[2], g[2] = {};
   float ss[2] = {0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < S; ++s) acc[s] = zero;
@@ -447,11 +447,19 @@ __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
     }
   };
   float* const stage = &sm.stage[wave][0][0];
+  // elements past the end count as zero, inputs, gains and weights alike: 0
+  // times an infinity would be NaN
+  const bool ragged = len % kTileChunk != 0 || (kHalf && total % 2 != 0);
   auto put = [&](int c) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       int q, m;
       const bool in = place(c, i, q, m);
+      if (ragged && !in) {
+        g[i] = zero;
+#pragma unroll
+        for (int t = 0; t < NT * S; ++t) w[t][i] = zero;
+      }
       f32x4 v[NT];
       v[0] = in ? x[i] : zero;
       if (MODE == kFusion) {

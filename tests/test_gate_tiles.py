@@ -8,6 +8,7 @@ up to 8192 terms of random sign err by about 2e-7 of their size (chains of at
 most four, 32 and four additions), and the five layers' errors add."""
 import numpy as np
 import pytest
+import torch
 
 import oda_synth as S
 from test_gate_parity import Gate, _check
@@ -41,3 +42,16 @@ def test_nonfinite_inputs_stay_in_their_request(kind, B):
     assert kind == "mlp" or (not np.isfinite(sc[2]) and fl[2] == 1)   # inf / inf in the norm
     keep = [b for b in range(B) if b not in (1, 2)]
     assert np.array_equal(sc[keep], clean[keep]) and not fl[keep].any()
+
+
+@pytest.mark.parametrize("d,dh,B", [(100, 28, 9), (1056, 32, 5), (1060, 2100, 70)])
+def test_an_infinite_weight_gives_an_infinite_score(d, dh, B):
+    """In the row's first elements too, which the chunk padding reads again."""
+    gate = Gate("mlp", d, dh, B, seed=d)
+    gate.params[0] = np.inf                               # W1[0][0]
+    gate.params[dh * d + dh] = 0.5                        # w2[0]
+    gate.dparams.copy_(torch.from_numpy(gate.params))
+    h, e, l = (x[0].copy() for x in S.gate_inputs(3, 1, B, d))
+    l[:, 0] = 1.0
+    sc, fl, _, _ = gate.run(h, e, l, 1e9)
+    assert np.all(sc == np.inf) and fl.all()
