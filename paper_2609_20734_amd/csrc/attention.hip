@@ -41,6 +41,7 @@
 #include "oda.h"
 #include "oda_device.h"
 #include "oda_internal.h"
+#include "oda_length_plan.h"
 
 namespace {
 
@@ -56,12 +57,9 @@ constexpr int kTargetShift = 8;
 constexpr int kTargetGroups = 1 << kTargetShift;   // workgroups a call aims for (one per CU)
 constexpr int kBalanceBlocks = 512;   // shortest split the plan adds to even out the CUs
 constexpr int kBalanceUnits = 64;     // units per request from which the plan evens out the CUs
-constexpr int kLengthBlocks = 128;    // below that: shortest split that the plan by length adds rounds for
-constexpr int kLengthRounds = 16;     // rounds of workgroups it considers
-constexpr int kLongBlocks = 1024;     // blocks per CU from which its splits are kLongSplit blocks
-constexpr int kLongSplit = 512;
 constexpr int kMergeChunk = 16;       // split partials read per round trip in the merge
 constexpr int kMergeSmall = 4;        // chunk used for the last few splits
+static_assert(oda::kPlanCus == (uint32_t)kTargetGroups && oda::kPlanWaves == (uint32_t)kWaves, "the plan by length's launch");
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -298,75 +296,12 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
 __device__ __forceinline__ uint32_t wave_total(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<false>(x), 63);
 }
-__device__ __forceinline__ uint32_t even_up(uint32_t x) { return (x + 1) & ~1u; }
 
 // One work item of a Full call: request, its length, its split of nsplit, and
 // the blocks per split.
 struct Item {
   int b, n, split, nsplit, bps;
 };
-
-// Blocks per split for up to 64 selected requests of nvb blocks each (per
-// lane; 0 where not selected or invalid) with `units` (layer, KV head) units
-// apiece.  Wavefront-uniform; the same in every workgroup of the call.
-//   - eight units per CU, whole units that fill their rounds of one workgroup
-//     per CU within 5%, or one round whose longest unit takes no longer alone
-//     (0.18 us a 128-wide block) than all blocks on a busy HBM (0.29 us a block
-//     and CU) and the merge (8 us): whole units.  24 requests of 200-2,000
-//     positions: 27.9 us, 35.8 split;
-//   - kLongBlocks blocks per CU: splits of kLongSplit blocks, whatever rounds
-//     that makes.  Many uneven rounds beat few even ones, whose workgroups
-//     start and wait for their first blocks together: one layer of 32
-//     requests of 8K-64K positions 721 us, in eight even rounds
-//     812, with the longest request's splits for all 913;
-//   - else, for m = 1, 2, ... rounds, the shortest splits whose (request,
-//     split) pairs fit m rounds; the first m at which they spread the blocks
-//     over the CUs within 10% of evenly, else the m with the least m * bps.
-//     Rounds past the first feasible one are tried only while splits keep
-//     kLengthBlocks blocks.
-template <int D>
-__device__ __forceinline__ uint32_t length_bps(const AttnArgs& a, uint32_t nvb, bool selected, uint32_t units) {
-  const uint32_t total = wave_total(nvb);
-  const uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<true>(nvb), 63);
-  const uint32_t count = (uint32_t)__popcll(__ballot(selected));
-  const uint32_t whole = even_up(max(longest, 2u));
-  const uint64_t work = (uint64_t)total * units;
-  const uint32_t rounds = (count * units + kTargetGroups - 1) >> kTargetShift;
-  if (rounds >= 8 || work * 20 >= ((uint64_t)rounds * whole << kTargetShift) * 19) return whole;
-  if (rounds == 1 && ((uint64_t)whole * 5 << kTargetShift) <= 8 * work + ((uint64_t)(240 * 128 / D) << kTargetShift)) return whole;
-  // no split shorter than a block per wavefront, no more splits than partial slots
-  const uint32_t least = even_up(max((uint32_t)kWaves, (longest + (uint32_t)a.max_splits - 1) / (uint32_t)a.max_splits));
-  const auto fits = [&](uint32_t c, uint32_t pairs) {
-    return wave_total(selected ? max(1u, (nvb + c - 1) / c) : 0u) <= pairs;
-  };
-  // the shortest splits that fit `pairs` (at bps there are at most total / bps + count)
-  const auto fit = [&](uint32_t pairs) {
-    for (uint32_t j = 0; j <= 3; ++j) {
-      const uint32_t room = 4 * pairs - j * count;
-      const uint32_t c = min(whole, max(least, even_up((4 * total + room - 1) / room)));
-      if (fits(c, pairs)) return c;
-    }
-    return whole;
-  };
-  const uint32_t slots = (uint32_t)a.pair_slots;
-  if (work >= (uint64_t)kLongBlocks << kTargetShift) {
-    const uint32_t c = min(whole, max(least, (uint32_t)kLongSplit));
-    return fits(c, slots) ? c : fit(slots);
-  }
-  uint32_t best = whole, best_m = 0;
-  for (uint32_t m = 1; m <= (uint32_t)kLengthRounds; ++m) {
-    const uint32_t pairs = min((uint32_t)kTargetGroups * m / units, slots);
-    if (pairs < count) continue;
-    if (best_m != 0 && work < ((uint64_t)kLengthBlocks * m << kTargetShift)) break;
-    const uint32_t c = fit(pairs);
-    if (best_m == 0 || m * c < best_m * best) {
-      best = c;
-      best_m = m;
-    }
-    if (work * 10 >= ((uint64_t)m * c << kTargetShift) * 9) break;
-  }
-  return best;
-}
 
 // The item of (request, split) pair `pair` of a Full call planned from the
 // selected requests' lengths: lane i holds the i-th listed request (list) or
@@ -390,10 +325,14 @@ __device__ __forceinline__ bool length_item(const AttnArgs& a, int active, uint3
   const int n = selected ? a.seq_lens[b] : 0;
   uint32_t nvb = 0;
   if (selected && n >= 1 && n <= a.max_len) nvb = (uint32_t)geometry(n, 0, a.window, a.has_cur).nvb;
-  uint32_t bps = length_bps<D>(a, nvb, selected, (uint32_t)a.L * (uint32_t)a.Hkv);
+  const uint32_t longest = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<true>(nvb), 63);
+  uint32_t bps = oda::length_bps(
+      wave_total(nvb), longest, (uint32_t)__popcll(__ballot(selected)), (uint32_t)a.L * (uint32_t)a.Hkv,
+      (uint32_t)a.max_splits, (uint32_t)a.pair_slots, (uint32_t)D,
+      [&](uint32_t c) { return wave_total(selected ? max(1u, (nvb + c - 1) / c) : 0u); });
   uint32_t splits = selected ? max(1u, (nvb + bps - 1) / bps) : 0u;
   if (splits > 1) {   // a request's splits of equal length
-    bps = even_up((nvb + splits - 1) / splits);
+    bps = oda::even_up((nvb + splits - 1) / splits);
     splits = (nvb + bps - 1) / bps;
   }
   const uint32_t upto = wave_scan<false>(splits);
@@ -1355,7 +1294,7 @@ oda_status run_attention(const oda_attn_shape* s, const oda_attn_inputs* in, boo
                 plan.nvb_max <= (1 << 23);
   int64_t slots = plan.full_slots;
   if (a.by_length) {
-    const int64_t rounds = select == kSelAll ? kLengthRounds : 2;
+    const int64_t rounds = select == kSelAll ? oda::kLengthRounds : 2;
     slots = std::max(slots, std::min(rounds * kTargetGroups / units, (int64_t)s->batch * plan.max_splits));
   }
   if (slots > INT32_MAX) return oda::fail(ODA_ERR_SHAPE, "grid too large (%lld request splits)", (long long)slots);

@@ -85,3 +85,37 @@ def test_an_empty_list_writes_nothing():
     out, lse = p.new_out(9.0)
     p.run_full(work_list=dev_i32([0, 0, 0, 0]), n_work=dev_i32([0]), out=out, lse=lse)
     assert torch.all(out == 9.0) and torch.all(lse == 9.0)
+
+
+def _aliased(seed, B, Hq, Hkv, D, seq, cur):
+    """A problem over long histories whose logical blocks share 96 physical ones."""
+    p = AttnProblem(seed, 1, B, Hq, Hkv, D, np.full(B, 16 * (96 // B), np.int32), cur=cur)
+    p.seq = np.asarray(seq, np.int32)
+    mb = -(-int(p.seq.max()) // 16)
+    p.table = S.rng(seed, S.STREAM_TABLE).integers(0, p.nb, (B, mb)).astype(np.int32)
+    p.shape = p.P.Shape(1, B, Hq, Hkv, D, mb, int(p.seq.max()), p.nb)
+    p.upload()
+    return p
+
+
+# blocks x units: 17,764 in one round; 69,888 and 133,120 in two and more rounds; 590,000 from
+# 1,024 blocks per CU, whose pairs are more than a list's grid holds
+@pytest.mark.parametrize("B,Hq,Hkv,D,lo,hi", [(6, 4, 2, 128, 3622, 43790), (5, 16, 8, 128, 7000, 48921),
+                                              (13, 20, 20, 64, 300, 16384), (8, 32, 32, 64, 8192, 65536)])
+@pytest.mark.parametrize("select", ["all", "flags", "list"])
+@pytest.mark.parametrize("cur", [False, True])
+def test_long_histories(B, Hq, Hkv, D, lo, hi, select, cur):
+    seq = [lo + (hi - lo) * i // (B - 1) for i in S.rng(B, S.STREAM_SEQ_LENS).permutation(B)]
+    p = _aliased(B + D, B, Hq, Hkv, D, seq, cur)
+    sel = dict(all={}, flags=dict(flags=dev_i32([1] * B)),
+               list=dict(work_list=dev_i32(list(range(B))[::-1]), n_work=dev_i32([B])))[select]
+    out, lse = (t.cpu().numpy() for t in p.run_full(**sel))
+    again, _ = p.run_full(**sel)
+    assert np.array_equal(out, again.cpu().numpy())
+    p.shape.split_blocks = 128
+    fout, flse = (t.cpu().numpy() for t in p.run_full(**sel))
+    assert np.abs(out - fout).max() <= MAX_ABS_INTERNAL and np.abs(lse - flse).max() <= MAX_ABS_INTERNAL
+    few = sorted({int(np.argmin(seq)), int(np.argmax(seq))}) if select == "all" else [int(np.argmin(seq))]
+    ro, rl = p.oracle_full(requests=few)[:2]
+    check_close(out[:, few], np.asarray(ro)[:, few], "out")
+    assert np.abs(lse[:, few] - np.asarray(rl)[:, few]).max() <= MAX_ABS_INTERNAL
