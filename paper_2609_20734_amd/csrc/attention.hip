@@ -1285,17 +1285,31 @@ oda_status run_attention(const oda_attn_shape* s, const oda_attn_inputs* in, boo
   // falls back on the device past 64).  With kBalanceUnits units or more per
   // request the plain plan's many workgroups even out by themselves, and each
   // workgroup's ~2 us of planning shows (8 layers, 3 requests: 600 us against
-  // 575).  The grid covers the pairs of the plain plan, and for
-  // the plan by length two rounds of workgroups, or as many as it may use
-  // when every request is selected anyway: workgroups without work cost a
-  // call about 5 ns each.
+  // 575).  So it does, without a gain, where every request is selected and
+  // even the longest lengths leave no splits of kLengthBlocks blocks for a
+  // round beyond two or more rounds of whole units (17 requests of 855-2,081
+  // positions, 6 layers of 8 KV heads: 97 us, 104 planned by length).
   const int64_t units = (int64_t)s->num_layers * s->num_kv_heads;
-  a.by_length = !local && plan.dyn && plan.max_splits > 1 && s->batch > 1 && units < kBalanceUnits && (select == kSelList || s->batch <= 64) &&
-                plan.nvb_max <= (1 << 23);
+  const int64_t whole_rounds = oda::ceil_div(s->batch * units, kTargetGroups);
+  const int64_t split_rounds = s->batch * units * plan.nvb_max / (kTargetGroups * (int64_t)oda::kLengthBlocks);
+  a.by_length = !local && plan.dyn && plan.max_splits > 1 && s->batch > 1 && units < kBalanceUnits &&
+                (select == kSelList || s->batch <= 64) && plan.nvb_max <= (1 << 23) &&
+                !(select == kSelAll && whole_rounds > 1 && split_rounds <= whole_rounds);
+  // The plan's grid covers every request whole and the rounds the plan may
+  // use.  Workgroups without work cost 2-6 ns each (32 equal requests of 1,024
+  // positions: 24.9 us, with sixteen rounds whatever the lengths 29.0), so it
+  // has no more rounds than the longest lengths can fill, and two for a list
+  // (few of whose requests are selected).  max_seq_len may be far above the
+  // lengths, so a call with every request selected stops at four rounds, or
+  // twice those of whole units: 32 requests of 1,024 positions under a limit of
+  // 65,536 take 26.1 us (sixteen rounds 35.3, two 24.7), of 8K-64K 770 us
+  // (sixteen 766, two 791).
   int64_t slots = plan.full_slots;
   if (a.by_length) {
-    const int64_t rounds = select == kSelAll ? oda::kLengthRounds : 2;
-    slots = std::max(slots, std::min(rounds * kTargetGroups / units, (int64_t)s->batch * plan.max_splits));
+    const int64_t most = select == kSelAll ? std::max<int64_t>(4, 2 * whole_rounds) : 2;
+    const int64_t rounds = std::max<int64_t>(1, std::min(most, split_rounds));
+    slots = std::min(rounds * kTargetGroups / units, (int64_t)s->batch * plan.max_splits);
+    slots = std::max<int64_t>(s->batch > 64 ? std::max(plan.full_slots, slots) : slots, s->batch);
   }
   if (slots > INT32_MAX) return oda::fail(ODA_ERR_SHAPE, "grid too large (%lld request splits)", (long long)slots);
   a.pair_slots = (int32_t)slots;

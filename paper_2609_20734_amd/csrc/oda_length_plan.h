@@ -58,8 +58,9 @@ ODA_PLAN_FN uint32_t shortest_fit(uint32_t total, uint32_t count, uint32_t least
 //   - eight units per CU, whole units that fill their rounds of one workgroup
 //     per CU within 5%, or one round whose longest unit takes no longer alone
 //     (0.18 us a 128-wide block) than all blocks on a busy HBM (0.29 us a block
-//     and CU) and the merge (8 us): whole units.  24 requests of 200-2,000
-//     positions: 27.9 us, 35.8 split;
+//     and CU) and the merge (8 us), or two rounds and more without the work
+//     for one more: whole units.  24 requests of 200-2,000 positions: 27.9 us,
+//     35.8 split;
 //   - kLongBlocks blocks per CU: splits of kLongSplit blocks, whatever rounds
 //     that makes.  Many uneven rounds beat few even ones, whose workgroups
 //     start and wait for their first blocks together: one layer of 32
@@ -78,6 +79,7 @@ ODA_PLAN_FN uint32_t length_bps(uint32_t total, uint32_t longest, uint32_t count
   const uint32_t rounds = (count * units + kPlanCus - 1) / kPlanCus;   // of whole units: the first feasible m
   if (rounds >= 8 || work * 20 >= (uint64_t)rounds * whole * kPlanCus * 19) return whole;
   if (rounds == 1 && (uint64_t)whole * 5 * kPlanCus <= 8 * work + 240 * 128 / head_dim * kPlanCus) return whole;
+  if (rounds > 1 && work < (uint64_t)kLengthBlocks * (rounds + 1) * kPlanCus) return whole;
   // no split shorter than a block per wavefront, no more splits than partial slots
   const uint32_t least = even_up(plan_max(kPlanWaves, (longest + max_splits - 1) / max_splits));
   if (work >= (uint64_t)kLongBlocks * kPlanCus) {

@@ -110,7 +110,8 @@ def test_random_lengths(plan, kind):
         work, rounds = sum(n) * units, -(-len(n) * units // CUS)
         least = (max(SHORTEST, -(-max(n) // max_splits)) + 1) & ~1
         if bps == whole and (rounds >= 8 or work * 20 >= rounds * whole * CUS * 19
-                             or (rounds == 1 and whole * 5 * CUS <= 8 * work + 240 * 128 // D * CUS)):
+                             or (rounds == 1 and whole * 5 * CUS <= 8 * work + 240 * 128 // D * CUS)
+                             or (rounds > 1 and work < ROUND_BLOCKS * (rounds + 1) * CUS)):
             continue
         if work >= LONG * CUS:
             c = min(whole, max(least, LONG_SPLIT))
