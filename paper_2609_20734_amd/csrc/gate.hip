@@ -938,13 +938,13 @@ oda_status check_gate(const oda_gate_desc* g) {
 
 template <int MODE, int R, int S, int BT = kBatchTile>
 void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
-  const int64_t items = a.rows / R;   // B <= BT: one batch tile
+  const int64_t items = a.rows / R * oda::ceil_div(a.B, BT);
   const int64_t groups = S == 1 ? oda::ceil_div(items, kWaves) : items;
   hipLaunchKernelGGL((gate_linear_kernel<MODE, R, S, BT>), dim3((unsigned)groups), dim3(256), 0, stream, a);
 }
 
 // Launch shape of a dense layer.  Four requests or more (five for the MLP
-// head's layer) take the matrix-core tiles: a call of the App. A.2 head at d =
+// head's layer, and see there) take the matrix-core tiles: a call of the App. A.2 head at d =
 // 4096, dt = 256 takes 32 us at 4-16 requests and 37 at 32, against 37 (4), 53
 // (8) and 64 (32) on the vector kernels, whose every few rows re-read all
 // requests' inputs (the d = 4328, dt = 436 head of 3: 42 against 39); the MLP
@@ -962,11 +962,21 @@ void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
 template <int MODE>
 void launch_linear(const LinArgs& a, hipStream_t stream) {
   if constexpr (MODE == kMlpHidden) {
-    // a long and wide layer of up to eight requests streams faster from
-    // 16-byte row loads: 5716 -> 928 of five 14.2 us against 15.8
-    if (a.B > kSmallBatchMlp && a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20))
-      return a.rows % 2 == 0 && a.rows >= 1024 ? launch_linear_rs<MODE, 2, kWaves, 8>(a, stream)
-                                               : launch_linear_rs<MODE, 1, kWaves, 8>(a, stream);
+    // A workgroup per row and eight requests where that is faster: a long and
+    // wide layer of up to eight requests streams faster from 16-byte row loads
+    // (5716 -> 928 of five 14.2 us against 15.8), and long rows are too few
+    // tiles, whose wavefronts walk K / 8 elements one wait after the other:
+    // 8192 -> 256 of five 10.4 against 14.9, of sixteen 16.7 against 17.6 (24:
+    // 18.6 against 18.3), 6144 -> 128 of 32 13.7 against 14.9, 8192 -> 512 of
+    // ten 19.0 against 18.2, 4096 -> 256 of six 8.8 against 9.7, of eight 10.4
+    // against 10.2.
+    if (a.B > kSmallBatchMlp) {
+      if (a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20) && a.rows % 2 == 0 && a.rows >= 1024)
+        return launch_linear_rs<MODE, 2, kWaves, 8>(a, stream);
+      if ((a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20)) || (a.B < 8 && a.K >= 4096) ||
+          (a.K >= 6144 && a.rows * oda::ceil_div(a.B, 8) <= 512))
+        return launch_linear_rs<MODE, 1, kWaves, 8>(a, stream);
+    }
   }
   if (a.B > (MODE == kMlpHidden ? kSmallBatchMlp : kSmallBatch)) return launch_tile<MODE>(a, stream);
   const int64_t items = a.rows;

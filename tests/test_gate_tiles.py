@@ -20,7 +20,10 @@ pytestmark = pytest.mark.gpu
     ("paper", 4, 4, 4), ("paper", 100, 64, 3), ("paper", 36, 12, 8), ("paper", 68, 20, 9), ("paper", 516, 36, 16), ("paper", 1028, 124, 17),
     ("paper", 2052, 260, 33), ("paper", 264, 1028, 4), ("paper", 4096, 132, 65), ("mlp", 4, 4, 5), ("mlp", 100, 28, 8),
     ("mlp", 1020, 2052, 6), ("mlp", 8192, 516, 17), ("mlp", 8192, 516, 7),
-    ("mlp", 4100, 1026 * 2, 8)])
+    ("mlp", 4100, 1026 * 2, 8),
+    # rows per workgroup instead of tiles, over one and several groups of eight requests, and past the limits
+    ("mlp", 4096, 36, 5), ("mlp", 4100, 516, 7), ("mlp", 6148, 68, 8), ("mlp", 6144, 132, 17), ("mlp", 8196, 256, 16),
+    ("mlp", 6144, 128, 30), ("mlp", 6144, 128, 33), ("mlp", 6140, 64, 9)])
 def test_tile_edges(kind, d, dh, B):
     gate = Gate(kind, d, dh, B, seed=d + dh)
     h, e, l = (x[0] for x in S.gate_inputs(d + B, 1, B, d))
