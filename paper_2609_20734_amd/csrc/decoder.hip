@@ -727,11 +727,16 @@ extern "C" oda_status oda_dense_bf16(const oda_dense_desc* desc, int32_t batch, 
   // requests 7.4 us with 8-row workgroups against 10.6 with 16, 32 requests
   // 11.7 with 16 against 19.9 with 8; gate and up 2048 -> 6144, 32 requests
   // 16.6 with 48 rows, 21.6 with 32, 19.9 with 16.  A layer of many rounds
-  // takes this path for one request too (2048 -> 151936: 104 us against 110).
+  // takes this path for one request too, where the wavefronts' stretches are
+  // whole chunks of lines: 2048 -> 151936 99 us against 105, 4096 -> 151936 205
+  // against 240, 1536 -> 65536 35.1 against 35.8, but 1624 -> 151936 97 against
+  // 83 and 2112 -> 151936 112 against 106.
   const auto groups_of = [&](int tiles, int edge) {
     return oda::ceil_div(N, tiles * edge) * oda::ceil_div(batch, edge);
   };
-  if ((batch > 1 || (!swiglu && groups_of(2, kMfmaRows) >= 8 * kTargetGroups)) && a.K < kMfmaMaxK) {
+  const bool one = !swiglu && groups_of(2, kMfmaRows) >= 8 * kTargetGroups && a.K >= 3 * kMfmaWaves * kChunk &&
+                   a.K % (kMfmaWaves * kChunk) == 0;
+  if ((batch > 1 || one) && a.K < kMfmaMaxK) {
     oda_status st;
     const auto fits = [&](int tiles, int edge) { return groups_of(tiles, edge) <= kTargetGroups; };
     if (swiglu) {

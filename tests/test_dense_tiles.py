@@ -107,8 +107,8 @@ def test_nonfinite_inputs_stay_in_their_request(B):
     assert np.array_equal(got[3:], clean[3:])
 
 
-@pytest.mark.parametrize("B,N", [(2, 24), (9, 24), (17, 5000), (1, 65552)])
-@pytest.mark.parametrize("K", [8, 136, 544, 1536])
+@pytest.mark.parametrize("K,N,B", [(K, N, B) for K in (8, 136, 544, 1536) for N, B in ((24, 2), (24, 9), (5000, 17))]
+                         + [(1536, 65552, 1)])
 def test_infinite_weights_and_gains(K, N, B):
     """A row with an infinite weight gives the infinity (or NaN) that a sum of
     its products gives, wherever in K it lies (the stretch padding repeats a
@@ -142,3 +142,15 @@ def test_infinite_weights_and_gains(K, N, B):
     x[B - 1, K - 1] = np.array([0x7f800001], np.uint32).view(np.float32)[0]
     y = run(x, None)
     assert np.all(np.isnan(y[B - 1])) and np.all(np.isfinite(y[:B - 1][:, clean]))
+
+
+@pytest.mark.parametrize("K,N", [(512, 65512), (1536, 65504), (1536, 65505), (1544, 65512), (2048, 65533)])
+def test_one_request_on_a_large_layer(K, N):
+    """On the tiles from 65,505 rows and K = 1536 in steps of 512, else a wavefront per rows."""
+    P = need_gpu()
+    g, W, x = _inputs(K + N, K, N, 1)
+    y = torch.empty(1, N, device="cuda")
+    P.dense_bf16(P.dense_desc(K, N, P.DENSE_PLAIN, dev_u16(W)), 1, dev_f32(x), None, y)
+    torch.cuda.synchronize()
+    ref = OD.dense(W, x, None, 1e-6, None)
+    assert np.all(np.abs(y.cpu().numpy() - ref) <= _bound(W, x.astype(np.float64), K) + 2.0 ** -23 * np.abs(ref))
