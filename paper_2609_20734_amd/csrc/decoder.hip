@@ -631,7 +631,9 @@ constexpr int kArgThreads = 1024;
 // maximum and number (five operations a group; tracking each value's index
 // took four times as many and, at 151,936 values, 16.7 us instead of 8.8).
 // The winning group is read again for the position.  kInFlight: 16-byte loads
-// in flight per thread (4 where one round of 4 covers the row).
+// in flight per thread (4 or 8 where one round of them covers the row: loads
+// past the end read its last group again, and 16 of them took 5.0 us at 16,400
+// values instead of 4.0).
 template <int kInFlight>
 __global__ __launch_bounds__(kArgThreads) void argmax_kernel(const float* x, int n, int32_t* index) {
   __shared__ float sv[kArgThreads / 64];
@@ -876,6 +878,8 @@ extern "C" oda_status oda_argmax(int32_t batch, int32_t n, const float* x, int32
   (void)hipGetLastError();
   if (n / 4 <= 4 * kArgThreads)
     hipLaunchKernelGGL(argmax_kernel<4>, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
+  else if (n / 4 <= 8 * kArgThreads)
+    hipLaunchKernelGGL(argmax_kernel<8>, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
   else
     hipLaunchKernelGGL(argmax_kernel<16>, dim3((unsigned)batch), dim3(kArgThreads), 0, stream, x, n, index);
   return launch_status();

@@ -12,7 +12,7 @@ from oracle import decoder as OD
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [4, 8, 4092, 16384, 16388, 65536, 65540, 151936])
+@pytest.mark.parametrize("n", [4, 8, 4092, 16384, 16388, 32768, 32772, 65536, 65540, 151936])
 def test_argmax_edges(n):
     P = need_gpu()
     g = S.rng(n, S.STREAM_DECODER)
