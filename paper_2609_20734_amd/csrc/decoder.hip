@@ -200,31 +200,34 @@ constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
 // x = p[0] + p[1] + p[2] with bf16 pieces, exactly where the last piece is no
 // subnormal (|x| from 2^-110): each piece is the leading eight significant bits
 // of what the ones before it leave (truncation, so no piece overflows).  An
-// infinity is its own first piece, and so is a quiet NaN.
+// infinity is its own first piece; a NaN stays one.
 __device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&p)[3]) {
   float r[8];
   float mx = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     r[e] = x[e];
-    mx = fmaxf(mx, fabsf(x[e]));
+    mx = __builtin_elementwise_maximum(mx, fabsf(x[e]));   // (a NaN if there is one)
   }
-  const bool inf = __any(mx == INFINITY);
+  const bool odd = __any(!(mx < INFINITY));
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     u32x4 w;
 #pragma unroll
     for (int e = 0; e < 4; ++e)   // the high halves of two floats
       w[e] = __builtin_amdgcn_perm(__float_as_uint(r[2 * e + 1]), __float_as_uint(r[2 * e]), 0x07060302u);
-    p[q] = __builtin_bit_cast(bf16x8, w);
     if (q < 2) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) r[e] -= __uint_as_float(__float_as_uint(r[e]) & 0xffff0000u);
-      if (q == 0 && inf) {
+      if (q == 0 && odd) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) r[e] = fabsf(x[e]) == INFINITY ? 0.f : r[e];
+        for (int e = 0; e < 8; ++e) {
+          if (x[e] != x[e]) w[e / 2] |= 0x40u << (16 * (e & 1));   // quiet: a NaN whose payload is cut stays one
+          r[e] = fabsf(x[e]) == INFINITY ? 0.f : r[e];
+        }
       }
     }
+    p[q] = __builtin_bit_cast(bf16x8, w);
   }
 }
 
@@ -384,19 +387,20 @@ void dense_mfma_kernel(DenseArgs p) {
     }
   };
   float (&stage)[kMfmaRows][kPitch] = sm.x[wave];
-  // Only a stretch's last chunk can reach past its end: there inputs, gains and
-  // weights are zeroed, all of them, since 0 times an infinity would be NaN.
+  // Only a stretch's last chunk can reach past its end (kHalf: the second
+  // half's, which is no longer than the first): there inputs, gains and weights
+  // are zeroed, all of them, since 0 times an infinity would be NaN.
+  const bool ragged = n % U != 0 || (step0 + n) * 32 > (kHalf ? p.K - khalf : p.K);
   auto put_x = [&](int c, bool last) {
 #pragma unroll
     for (int m = 0; m < kPairs; ++m) {
       f32x4 v = x[m], gk = g[kHalf && m >= kPairs / 2 ? 1 : 0];
-      if (last && kx + c * kChunk >= (kHalf && m >= kPairs / 2 ? stop1 : stop0)) v = gk = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (last) {
+        if (kx + c * kChunk >= (kHalf && m >= kPairs / 2 ? stop1 : stop0)) v = gk = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
       if (kNorm) {
         ss[m] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
         v = f32x4{v[0] * gk[0], v[1] * gk[1], v[2] * gk[2], v[3] * gk[3]};
-      } else {   // NaNs quiet (the product does so above): truncated to bf16 they stay NaNs
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __builtin_canonicalizef(v[e]);
       }
       *reinterpret_cast<f32x4*>(&stage[kRowsAt * m + lane / kLanes][4 * (lane % kLanes)]) = v;
     }
@@ -404,9 +408,11 @@ void dense_mfma_kernel(DenseArgs p) {
   auto put_w = [&](int c, bool last) {
 #pragma unroll
     for (int i = 0; i < kWLoads; ++i) {
-      if (last && kw + c * kChunk >= (kHalf && i == 1 ? stop1 : stop0)) {
+      if (last) {
+        if (kw + c * kChunk >= (kHalf && i == 1 ? stop1 : stop0)) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) w[s][i] = u32x4{0u, 0u, 0u, 0u};
+          for (int s = 0; s < S; ++s) w[s][i] = u32x4{0u, 0u, 0u, 0u};
+        }
       }
 #pragma unroll
       for (int s = 0; s < S; ++s)
@@ -443,8 +449,8 @@ void dense_mfma_kernel(DenseArgs p) {
 #pragma unroll
       for (int u = 0; u < U; ++u) step(u);
     }
-    put_x(chunks - 1, true);
-    put_w(chunks - 1, true);
+    put_x(chunks - 1, ragged);
+    put_w(chunks - 1, ragged);
 #pragma unroll
     for (int u = 0; u < U; ++u) step(u);
   }
