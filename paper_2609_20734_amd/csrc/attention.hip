@@ -297,6 +297,10 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<false>(x), 63);
 }
 
+__device__ __forceinline__ uint32_t split_count(uint32_t n, uint32_t c) {
+  return oda::ceil_quotient(n, c, __builtin_amdgcn_rcpf((float)c));
+}
+
 // One work item of a Full call: request, its length, its split of nsplit, and
 // the blocks per split.
 struct Item {
@@ -329,11 +333,11 @@ __device__ __forceinline__ bool length_item(const AttnArgs& a, int active, uint3
   uint32_t bps = oda::length_bps(
       wave_total(nvb), longest, (uint32_t)__popcll(__ballot(selected)), (uint32_t)a.L * (uint32_t)a.Hkv,
       (uint32_t)a.max_splits, (uint32_t)a.pair_slots, (uint32_t)D,
-      [&](uint32_t c) { return wave_total(selected ? max(1u, (nvb + c - 1) / c) : 0u); });
-  uint32_t splits = selected ? max(1u, (nvb + bps - 1) / bps) : 0u;
+      [&](uint32_t c) { return wave_total(selected ? max(1u, split_count(nvb, c)) : 0u); });
+  uint32_t splits = selected ? max(1u, split_count(nvb, bps)) : 0u;
   if (splits > 1) {   // a request's splits of equal length
-    bps = oda::even_up((nvb + splits - 1) / splits);
-    splits = (nvb + bps - 1) / bps;
+    bps = oda::even_up(split_count(nvb, splits));
+    splits = split_count(nvb, bps);
   }
   const uint32_t upto = wave_scan<false>(splits);
   const uint64_t before = __ballot(upto <= pair);
@@ -1293,7 +1297,7 @@ oda_status run_attention(const oda_attn_shape* s, const oda_attn_inputs* in, boo
   const int64_t whole_rounds = oda::ceil_div(s->batch * units, kTargetGroups);
   const int64_t split_rounds = s->batch * units * plan.nvb_max / (kTargetGroups * (int64_t)oda::kLengthBlocks);
   a.by_length = !local && plan.dyn && plan.max_splits > 1 && s->batch > 1 && units < kBalanceUnits &&
-                (select == kSelList || s->batch <= 64) && plan.nvb_max <= (1 << 23) &&
+                (select == kSelList || s->batch <= 64) && plan.nvb_max <= (1 << 20) &&
                 !(select == kSelAll && whole_rounds > 1 && split_rounds <= whole_rounds);
   // The plan's grid covers every request whole and the rounds the plan may
   // use.  Workgroups without work cost 2-6 ns each (32 equal requests of 1,024

@@ -26,6 +26,15 @@ ODA_PLAN_FN uint32_t plan_min(uint32_t x, uint32_t y) { return x < y ? x : y; }
 ODA_PLAN_FN uint32_t plan_max(uint32_t x, uint32_t y) { return x > y ? x : y; }
 ODA_PLAN_FN uint32_t even_up(uint32_t x) { return (x + 1) & ~1u; }
 
+// ceil(n / c) for n up to 2^20 and c from 1, with inv = 1 / c to within 2^-22 of
+// it: n * inv rounded is the quotient's floor or ceiling (its error stays below
+// a half), and one product tells which.  Half the instructions of a 32-bit
+// division, on the way to every workgroup's first load.
+ODA_PLAN_FN uint32_t ceil_quotient(uint32_t n, uint32_t c, float inv) {
+  const uint32_t q = (uint32_t)((float)n * inv + 0.5f);
+  return q * c < n ? q + 1 : q;
+}
+
 // The shortest even split length c in [least, whole], to within 1/16 of it,
 // whose (request, split) pairs are at most `pairs` (pairs >= count; `total`
 // blocks in `count` requests; pairs_of(c) = the sum of max(1, ceil(blocks / c))

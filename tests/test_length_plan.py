@@ -14,10 +14,31 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CUS, SHORTEST, ROUND_BLOCKS, ROUNDS, LONG, LONG_SPLIT = 256, 8, 128, 16, 1024, 512
 
 PROGRAM = r"""
+#include <cmath>
 #include <cstdio>
 #include <vector>
 #include "oda_length_plan.h"
-int main() {
+static unsigned plan_less(unsigned most, int i) { return most < (unsigned)i ? most : (unsigned)i; }
+int main(int argc, char**) {
+  if (argc > 1) {   // quotients: every c below 2^16 and some above, n around its multiples, inv off by an ulp or two
+    unsigned bad = 0, state = 1;
+    for (unsigned c = 1; c < (1u << 20); c += c < (1u << 16) ? 1 : 997)
+      for (int i = 0; i < 40; ++i) {
+        state = state * 1664525u + 1013904223u;
+        const unsigned most = (1u << 20) / c, k = i < 3 ? most - plan_less(most, i) : state % (most + 1);
+        for (int d = -1; d <= 1; ++d) {
+          const long long n = (long long)k * c + d;
+          if (n < 0 || n > (1 << 20)) continue;
+          for (int u = -2; u <= 2; ++u) {
+            float inv = 1.0f / (float)c;
+            for (int j = 0; j < (u < 0 ? -u : u); ++j) inv = std::nextafter(inv, u < 0 ? 0.f : 2.f);
+            bad += oda::ceil_quotient((unsigned)n, c, inv) != (unsigned)((n + c - 1) / c);
+          }
+        }
+      }
+    std::printf("%u\n", bad);
+    return 0;
+  }
   unsigned units, max_splits, slots, head_dim, pairs, count;
   while (std::scanf("%u %u %u %u %u %u", &units, &max_splits, &slots, &head_dim, &pairs, &count) == 6) {
     std::vector<unsigned> n(count);
@@ -55,6 +76,8 @@ def plan(tmp_path_factory):
                     "-o", str(d / "plan")], check=True)
 
     def run(cases):
+        if cases is None:
+            return subprocess.run([str(d / "plan"), "quotients"], capture_output=True, text=True, check=True, timeout=60).stdout
         """(units, max_splits, slots, head_dim, pairs, blocks) -> (shortest_fit, its trials, length_bps)."""
         text = "\n".join(" ".join(map(str, [*c[:5], len(c[5]), *c[5]])) for c in cases)
         out = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True, timeout=60).stdout
@@ -133,3 +156,8 @@ def test_evenly_spread_lengths_are_split(plan):
     n = [227, 729, 1231, 1733, 2235, 2737]
     (fit, _, bps), = plan([(2, 42, 256, 128, 128, n)])
     assert _exact(n, SHORTEST, 128)[0] == 74 and fit <= 78 and bps <= 78
+
+
+def test_quotients(plan):
+    """ceil_quotient is exact over its range with a reciprocal two units off."""
+    assert int(plan(None)) == 0
