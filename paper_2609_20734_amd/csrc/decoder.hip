@@ -446,11 +446,14 @@ void dense_mfma_kernel(DenseArgs p) {
       load_x(c + 1);
       put_w(c, false);
       load_w(c + 1);
+      oda::wave_lds_fence();
 #pragma unroll
       for (int u = 0; u < U; ++u) step(u);
+      oda::wave_lds_fence();
     }
     put_x(chunks - 1, ragged);
     put_w(chunks - 1, ragged);
+    oda::wave_lds_fence();
 #pragma unroll
     for (int u = 0; u < U; ++u) step(u);
   }

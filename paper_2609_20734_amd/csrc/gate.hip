@@ -32,6 +32,7 @@
 #include <utility>
 
 #include "oda.h"
+#include "oda_device.h"
 #include "oda_internal.h"
 
 namespace {
@@ -513,9 +514,12 @@ __global__ __launch_bounds__(kTileWaves * 64) void gate_tile_kernel(LinArgs p) {
     for (int c = c0; c + 1 < c1; ++c) {
       put(c, false);
       load(c + 1);
+      oda::wave_lds_fence();
       multiply();
+      oda::wave_lds_fence();
     }
     put(c1 - 1, true);
+    oda::wave_lds_fence();
     multiply();
   }
 

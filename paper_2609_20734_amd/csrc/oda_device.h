@@ -15,6 +15,16 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
   return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Orders a wavefront's shared-memory stores before the loads of its other lanes
+// that follow, and these before the next stores, where a wavefront alone uses
+// its part of LDS.  The hardware keeps one wavefront's LDS operations in order;
+// this tells the compiler that the lanes communicate.  No instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Rotary frequency of dims i and i + D/2 (lane i): theta^(-2i/D), from
 // log2(theta) formed on the host (relative error below 2^-49).
 __device__ __forceinline__ double rope_frequency(int lane, int D, double log2_theta) {
