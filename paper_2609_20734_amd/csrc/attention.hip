@@ -685,14 +685,14 @@ __device__ __forceinline__ void merge_unit(const AttnArgs& a, int l, int b, int 
 // Fused calls: the unit's G query heads, its K head and its V head of the
 // current token, from the fp32 QKV projection output (q heads, then k heads,
 // then v heads per request), one head per wavefront: q and k through the
-// per-head RMSNorm and the rotary embedding at position n_raw - 1 (the shared
+// per-head RMSNorm and the rotary embedding at position n - 1 (the shared
 // oda::head_norm and rotate_pair, the same code oda_qk_norm_rope runs), v
 // unchanged, all rounded to bf16 into prep = [G][D] query rows, then K, then
-// V.  Only the rotation needs the length: the head is read, normalised and
-// its frequencies formed while the length is on its way.  Returns it.
+// V.  Only the rotation uses the length n (any value: an invalid one is found
+// out afterwards).
 template <int D>
-__device__ __forceinline__ int prepare_current(const AttnArgs& a, int b, int g, int n_raw, uint16_t* prep,
-                                               bool write_out) {
+__device__ __forceinline__ void prepare_current(const AttnArgs& a, int b, int g, int n, uint16_t* prep,
+                                                bool write_out) {
   constexpr int half = D / 2;
   const int G = a.G;
   const int lane = threadIdx.x & 63;
@@ -706,7 +706,7 @@ __device__ __forceinline__ int prepare_current(const AttnArgs& a, int b, int g, 
     float x2 = lane < half ? src[lane + half] : 0.f;
     if (t <= G) {
       oda::head_norm(x1, x2, lane < half, lane, D, t < G ? a.q_gain : a.k_gain, a.rms_eps);
-      oda::rotate_pair(x1, x2, (double)(n_raw - 1), frequency);
+      oda::rotate_pair(x1, x2, (double)(n - 1), frequency);
     }
     if (lane < half) {
       const uint16_t y1 = oda::bf16_rne(x1), y2 = oda::bf16_rne(x2);
@@ -720,7 +720,6 @@ __device__ __forceinline__ int prepare_current(const AttnArgs& a, int b, int g, 
       }
     }
   }
-  return n_raw;
 }
 
 // One unit of work: the wavefront runs of r (this split of request b) for
@@ -908,22 +907,21 @@ void attn_split_kernel(AttnArgs a) {
   }
   const int b = it.b, split = it.split, bps = it.bps;
   const int G = a.G;
-  int n;
   CurSrc cur;
   if (a.qkv != nullptr) {
     // fused call: this workgroup builds the unit's bf16 query rows and the
     // candidate K/V in shared memory (every split the same values); split 0
     // also writes the candidate out for the commit
     uint16_t* prep = reinterpret_cast<uint16_t*>(smem + split_lds_floats(G, D));
-    n = uniform(prepare_current<D>(a, b, g, it.n, prep, split == 0));
+    prepare_current<D>(a, b, g, it.n, prep, split == 0);
     __syncthreads();
     cur.q = prep;
     cur.k = prep + G * D;
     cur.v = prep + (G + 1) * D;
   } else {
-    n = uniform(it.n);
     cur = global_cur(a, D, l, b, g);
   }
+  const int n = uniform(it.n);
   if (!valid_len(a, n)) {   // no history is addressed: the request's rows become NaN
     if (split == 0) {
       const int64_t q0 = (((int64_t)l * a.B + b) * a.Hq + (int64_t)g * G) * D;

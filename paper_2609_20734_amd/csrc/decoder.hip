@@ -305,7 +305,7 @@ void dense_mfma_kernel(DenseArgs p) {
   static_assert(!kHalf || (kMfmaRows / kRowsAt == 4 && kWLoads == 2), "a load stays within one half");
   const int stop0 = min(khalf, (step0 + n) * 32), stop1 = min(p.K - khalf, (step0 + n) * 32);
 
-  // input row 2m + lane / 32 of load m: its request's row (columns past the
+  // input row 4m + lane / 16 of load m: its request's row (columns past the
   // last request repeat it and are not stored; a listed request outside
   // [0, B) is computed as request 0 and not stored) and half of K
   const float* xrow[kPairs];

@@ -79,7 +79,8 @@ __device__ __forceinline__ float4 load4_or_zero(const float* p, const float* saf
   return ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// One dense layer for a (row group, batch tile) item.  R consecutive output
+// One dense layer for a (row group, batch tile of BT requests) item; only the
+// MLP head's layer has more than one batch tile here.  R consecutive output
 // rows share every load of the inputs (R > 1 when several requests are
 // batched, so the inputs are not re-read per row); S wavefronts of the
 // workgroup split K between them, chunk c going to wavefront c mod S (S = 4
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
   const float* wrow = W + (int64_t)row0 * p.K;
   const float* wrow2 = kTwo ? p.W2 + (int64_t)row0 * p.K : nullptr;
   // the epilogue's bias or residual for the output this lane will hold (lane
-  // j * 8 + bi: row j, request bi), read now so it is not a dependent load
+  // j * BT + bi: row j, request bi), read now so it is not a dependent load
   // after the reduction; clamped to a valid element for lanes without one
   float epi = 0.f;
   if (MODE != kGateUp) {
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
   }
   if (full % S == part && full * 256 + 4 * lane < p.K) step(full * 256 + 4 * lane);
 
-  // reduce over the wavefront; lane j * 8 + bi keeps row j, request bi
+  // reduce over the wavefront; lane j * BT + bi keeps row j, request bi
   float v = 0.f, v2 = 0.f, my_ss = 0.f;
 #pragma unroll
   for (int bi = 0; bi < BT; ++bi) {
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(256) void gate_linear_kernel(LinArgs p) {
       for (int w = 1; w < S; ++w) my_ss += sm[w][(kTwo ? 2 : 1) * kAcc + bi];
     }
   } else if (kNorm) {
-    my_ss = __shfl(my_ss, lane % BT);   // lane j * 8 + bi needs request bi's sum of squares
+    my_ss = __shfl(my_ss, lane % BT);   // lane j * BT + bi needs request bi's sum of squares
   }
   const int j = lane / BT, bi = lane % BT;
   if (lane >= kAcc || bi >= nb) return;
