@@ -33,8 +33,24 @@ def _inputs(seed, K, rows, B):
     return g, W, x
 
 
+PLAIN = [(1, 2), (8, 8), (17, 9), (33, 16), (2050, 3), (2056, 17), (4112, 33), (8208, 7), (2048, 32), (2041, 31)]
+SWIGLU = [(8, 5, 2), (72, 17, 8), (520, 2056, 4), (1000, 4104, 16), (2048, 6152, 3), (264, 6160, 33), (264, 6144, 8),
+          (520, 6137, 7), (136, 4096, 16), (1000, 4089, 15)]
+
+
+def _tile(swiglu, N, B):
+    """Row tiles and tile edge of the launch: the narrowest with one workgroup per CU at most, else the widest."""
+    shapes = [(1, 8), (2, 8)] + ([(3, 8)] if swiglu else []) + [(1, 16), (2, 16)] + ([(3, 16)] if swiglu else [])
+    return next((t for t in shapes if -(-N // (t[0] * t[1])) * -(-B // t[1]) <= 256), shapes[-1])
+
+
+def test_every_tile_shape_is_among_the_cases():
+    assert {_tile(False, N, B) for N, B in PLAIN} == {(1, 8), (2, 8), (1, 16), (2, 16)}
+    assert {_tile(True, N, B) for _, N, B in SWIGLU} == {(p, e) for p in (1, 2, 3) for e in (8, 16)}
+
+
 @pytest.mark.parametrize("K", [8, 40, 264, 1000, 2088])
-@pytest.mark.parametrize("N,B", [(1, 2), (8, 8), (17, 9), (33, 16), (2050, 3), (2056, 17), (4112, 33), (8208, 7)])
+@pytest.mark.parametrize("N,B", PLAIN)
 def test_plain_tiles(K, N, B):
     P = need_gpu()
     g, W, x = _inputs(K * 7 + N + B, K, N, B)
@@ -50,8 +66,7 @@ def test_plain_tiles(K, N, B):
     assert np.all(np.abs(y.cpu().numpy() - ref) <= _bound(W, xn, K) + 2.0 ** -23 * np.abs(ref))
 
 
-@pytest.mark.parametrize("K,N,B", [(8, 5, 2), (72, 17, 8), (520, 2056, 4), (1000, 4104, 16), (2048, 6152, 3),
-                                   (264, 6160, 33)])
+@pytest.mark.parametrize("K,N,B", SWIGLU)
 def test_swiglu_tiles_with_a_list(K, N, B):
     P = need_gpu()
     g, W, x = _inputs(K + N + B, K, 2 * N, B)

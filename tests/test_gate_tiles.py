@@ -16,14 +16,31 @@ from test_gate_parity import Gate, _check
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kind,d,dh,B", [
+CASES = [
     ("paper", 4, 4, 4), ("paper", 100, 64, 3), ("paper", 36, 12, 8), ("paper", 68, 20, 9), ("paper", 516, 36, 16), ("paper", 1028, 124, 17),
     ("paper", 2052, 260, 33), ("paper", 264, 1028, 4), ("paper", 4096, 132, 65), ("mlp", 4, 4, 5), ("mlp", 100, 28, 8),
     ("mlp", 1020, 2052, 6), ("mlp", 8192, 516, 17), ("mlp", 8192, 516, 7),
     ("mlp", 4100, 1026 * 2, 8),
     # rows per workgroup instead of tiles, over one and several groups of eight requests, and past the limits
     ("mlp", 4096, 36, 5), ("mlp", 4100, 516, 7), ("mlp", 6148, 68, 8), ("mlp", 6144, 132, 17), ("mlp", 8196, 256, 16),
-    ("mlp", 6144, 128, 30), ("mlp", 6144, 128, 33), ("mlp", 6140, 64, 9)])
+    ("mlp", 6144, 128, 30), ("mlp", 6144, 128, 33), ("mlp", 6140, 64, 9),
+    # tiles of sixteen rows and requests
+    ("paper", 516, 632, 70), ("paper", 1028, 1028, 40), ("mlp", 260, 1028, 70), ("mlp", 4100, 1028, 40)]
+
+
+def test_both_tile_edges_are_among_the_cases():
+    """Eight rows and requests up to 512 workgroups of them, else sixteen, for every layer of either head."""
+    seen = set()
+    for kind, _, dh, B in CASES:
+        tall = B > (3 if kind == "paper" else 4)
+        for layer, rows in (("tower", 3 * -(-dh // 8)), ("fusion", -(-dh // 8)), ("gate/up", -(-2 * dh // 8)),
+                            ("down", -(-dh // 8))) if kind == "paper" else (("mlp", -(-dh // 8)),):
+            if tall:
+                seen.add((layer, rows * -(-B // 8) <= 512))
+    assert len(seen) == 10
+
+
+@pytest.mark.parametrize("kind,d,dh,B", CASES)
 def test_tile_edges(kind, d, dh, B):
     gate = Gate(kind, d, dh, B, seed=d + dh)
     h, e, l = (x[0] for x in S.gate_inputs(d + B, 1, B, d))
