@@ -90,7 +90,7 @@ struct AttnArgs {
   int32_t dyn_splits;       // 1: blocks per split chosen on the device (effective_bps)
   int32_t split_cap;        // most splits per unit the automatic plan considers
   int32_t nvb_max;          // host bound on visited blocks per request
-  int32_t by_length;        // Full: splits chosen on the device from the selected requests' lengths (length_plan)
+  int32_t by_length;        // Full: splits chosen on the device from the selected requests' lengths (length_item)
   int32_t pair_slots;       // (request, split) pairs the grid covers
   int32_t lpi;              // layers per work item (attn_local_layers_kernel)
   int32_t select;
@@ -297,10 +297,6 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan<false>(x), 63);
 }
 
-__device__ __forceinline__ uint32_t split_count(uint32_t n, uint32_t c) {
-  return oda::ceil_quotient(n, c, __builtin_amdgcn_rcpf((float)c));
-}
-
 // One work item of a Full call: request, its length, its split of nsplit, and
 // the blocks per split.
 struct Item {
@@ -315,6 +311,20 @@ struct Item {
 // last pair.
 template <int D>
 __device__ __forceinline__ bool length_item(const AttnArgs& a, int active, uint32_t pair, Item& it) {
+  if (active == 1) {   // one request: its plan on scalars, without the lanes' loads and scans
+    if (!request_of_rank(a, 0, it.b)) return false;
+    it.b = uniform(it.b);
+    it.n = a.seq_lens[it.b];
+    const uint32_t n1 = it.n >= 1 && it.n <= a.max_len ? (uint32_t)geometry(it.n, 0, a.window, a.has_cur).nvb : 0u;
+    const auto splits_of = [&](uint32_t c) { return max(1u, oda::ceil_quotient(n1, c)); };
+    uint32_t c = oda::length_bps(n1, n1, 1u, (uint32_t)a.L * (uint32_t)a.Hkv, (uint32_t)a.max_splits, (uint32_t)a.pair_slots,
+                                 (uint32_t)D, splits_of);
+    c = oda::even_up(max(2u, oda::ceil_quotient(n1, splits_of(c))));
+    it.bps = uniform((int)c);
+    it.nsplit = uniform((int)splits_of(c));
+    it.split = (int)pair;
+    return it.split < it.nsplit;
+  }
   const int lane = (int)(threadIdx.x & 63);
   int b = lane;
   bool selected;
@@ -333,11 +343,11 @@ __device__ __forceinline__ bool length_item(const AttnArgs& a, int active, uint3
   uint32_t bps = oda::length_bps(
       wave_total(nvb), longest, (uint32_t)__popcll(__ballot(selected)), (uint32_t)a.L * (uint32_t)a.Hkv,
       (uint32_t)a.max_splits, (uint32_t)a.pair_slots, (uint32_t)D,
-      [&](uint32_t c) { return wave_total(selected ? max(1u, split_count(nvb, c)) : 0u); });
-  uint32_t splits = selected ? max(1u, split_count(nvb, bps)) : 0u;
+      [&](uint32_t c) { return wave_total(selected ? max(1u, oda::ceil_quotient(nvb, c)) : 0u); });
+  uint32_t splits = selected ? max(1u, oda::ceil_quotient(nvb, bps)) : 0u;
   if (splits > 1) {   // a request's splits of equal length
-    bps = oda::even_up(split_count(nvb, splits));
-    splits = split_count(nvb, bps);
+    bps = oda::even_up(oda::ceil_quotient(nvb, splits));
+    splits = oda::ceil_quotient(nvb, bps);
   }
   const uint32_t upto = wave_scan<false>(splits);
   const uint64_t before = __ballot(upto <= pair);

@@ -26,13 +26,21 @@ ODA_PLAN_FN uint32_t plan_min(uint32_t x, uint32_t y) { return x < y ? x : y; }
 ODA_PLAN_FN uint32_t plan_max(uint32_t x, uint32_t y) { return x > y ? x : y; }
 ODA_PLAN_FN uint32_t even_up(uint32_t x) { return (x + 1) & ~1u; }
 
-// ceil(n / c) for n up to 2^20 and c from 1, with inv = 1 / c to within 2^-22 of
-// it: n * inv rounded is the quotient's floor or ceiling (its error stays below
-// a half), and one product tells which.  Half the instructions of a 32-bit
-// division, on the way to every workgroup's first load.
+// ceil(n / c), c from 1, for n up to 2^26 and quotients up to 2^20 (a larger
+// one comes out above 2^19: callers bound it by a request's blocks), with inv = 1 / c to within 2^-22 of it: n * inv
+// rounded is the quotient's floor or ceiling (its error stays below a half), and
+// one product tells which.  A third of the instructions of a 32-bit division, on
+// the way to every workgroup's first load.
 ODA_PLAN_FN uint32_t ceil_quotient(uint32_t n, uint32_t c, float inv) {
   const uint32_t q = (uint32_t)((float)n * inv + 0.5f);
   return q * c < n ? q + 1 : q;
+}
+ODA_PLAN_FN uint32_t ceil_quotient(uint32_t n, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return ceil_quotient(n, c, __builtin_amdgcn_rcpf((float)c));
+#else
+  return ceil_quotient(n, c, 1.f / (float)c);
+#endif
 }
 
 // The shortest even split length c in [least, whole], to within 1/16 of it,
@@ -45,9 +53,9 @@ ODA_PLAN_FN uint32_t ceil_quotient(uint32_t n, uint32_t c, float inv) {
 template <class PairsOf>
 ODA_PLAN_FN uint32_t shortest_fit(uint32_t total, uint32_t count, uint32_t least, uint32_t whole, uint32_t pairs,
                                   const PairsOf& pairs_of) {
-  uint32_t lo = plan_min(whole, plan_max(least, even_up((total + pairs - 1) / pairs)));
+  uint32_t lo = plan_min(whole, plan_max(least, even_up(ceil_quotient(total, pairs))));
   uint32_t hi = whole;
-  if (pairs > count) hi = plan_max(lo, plan_min(whole, even_up((total + pairs - count - 1) / (pairs - count))));
+  if (pairs > count) hi = plan_max(lo, plan_min(whole, even_up(ceil_quotient(total, pairs - count))));
   uint32_t c = lo;
   for (;;) {
     if (pairs_of(c) <= pairs) {
@@ -61,9 +69,10 @@ ODA_PLAN_FN uint32_t shortest_fit(uint32_t total, uint32_t count, uint32_t least
   }
 }
 
-// Blocks per split for `count` selected requests of `total` blocks together,
-// the longest of `longest`, with `units` (layer, KV head) units apiece, at most
-// max_splits splits each and at most `slots` (request, split) pairs (>= count).
+// Blocks per split for `count` (at most 64) selected requests of `total` blocks
+// together, the longest of `longest` (at most 2^20), with `units` (layer, KV
+// head) units apiece, at most max_splits splits each and at most `slots`
+// (request, split) pairs (>= count).
 //   - eight units per CU, whole units that fill their rounds of one workgroup
 //     per CU within 5%, or one round whose longest unit takes no longer alone
 //     (0.18 us a 128-wide block) than all blocks on a busy HBM (0.29 us a block
@@ -90,7 +99,7 @@ ODA_PLAN_FN uint32_t length_bps(uint32_t total, uint32_t longest, uint32_t count
   if (rounds == 1 && (uint64_t)whole * 5 * kPlanCus <= 8 * work + 240 * 128 / head_dim * kPlanCus) return whole;
   if (rounds > 1 && work < (uint64_t)kLengthBlocks * (rounds + 1) * kPlanCus) return whole;
   // no split shorter than a block per wavefront, no more splits than partial slots
-  const uint32_t least = even_up(plan_max(kPlanWaves, (longest + max_splits - 1) / max_splits));
+  const uint32_t least = even_up(plan_max(kPlanWaves, ceil_quotient(longest, max_splits)));
   if (work >= (uint64_t)kLongBlocks * kPlanCus) {
     const uint32_t c = plan_min(whole, plan_max(least, kLongSplit));
     return pairs_of(c) <= slots ? c : shortest_fit(total, count, least, whole, slots, pairs_of);
@@ -98,7 +107,8 @@ ODA_PLAN_FN uint32_t length_bps(uint32_t total, uint32_t longest, uint32_t count
   uint32_t best = whole, best_m = 0;
   for (uint32_t m = rounds; m <= kLengthRounds; ++m) {
     if (best_m != 0 && work < (uint64_t)kLengthBlocks * m * kPlanCus) break;
-    const uint32_t c = shortest_fit(total, count, least, whole, plan_min(kPlanCus * m / units, slots), pairs_of);
+    const uint32_t pairs = ceil_quotient(kPlanCus * m - units + 1, units);   // the floor of kPlanCus * m / units
+    const uint32_t c = shortest_fit(total, count, least, whole, plan_min(pairs, slots), pairs_of);
     if (best_m == 0 || m * c < best_m * best) {
       best = c;
       best_m = m;

@@ -22,13 +22,13 @@ static unsigned plan_less(unsigned most, int i) { return most < (unsigned)i ? mo
 int main(int argc, char**) {
   if (argc > 1) {   // quotients: every c below 2^16 and some above, n around its multiples, inv off by an ulp or two
     unsigned bad = 0, state = 1;
-    for (unsigned c = 1; c < (1u << 20); c += c < (1u << 16) ? 1 : 997)
+    for (unsigned c = 1; c < (1u << 24); c += c < (1u << 16) ? 1 : 997)
       for (int i = 0; i < 40; ++i) {
         state = state * 1664525u + 1013904223u;
-        const unsigned most = (1u << 20) / c, k = i < 3 ? most - plan_less(most, i) : state % (most + 1);
+        const unsigned most = oda::plan_min((1u << 26) / c, 1u << 20), k = i < 3 ? most - plan_less(most, i) : state % (most + 1);
         for (int d = -1; d <= 1; ++d) {
           const long long n = (long long)k * c + d;
-          if (n < 0 || n > (1 << 20)) continue;
+          if (n < 0 || n > (1 << 26) || n > (1ll << 20) * c) continue;
           for (int u = -2; u <= 2; ++u) {
             float inv = 1.0f / (float)c;
             for (int j = 0; j < (u < 0 ? -u : u); ++j) inv = std::nextafter(inv, u < 0 ? 0.f : 2.f);
