@@ -79,9 +79,10 @@ __device__ __forceinline__ float4 load4_or_zero(const float* p, const float* saf
   return ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// One dense layer for a (row group, batch tile of BT requests) item; only the
-// MLP head's layer has more than one batch tile here.  R consecutive output
-// rows share every load of the inputs (R > 1 when several requests are
+// One dense layer for a (row group, batch tile of BT requests) item (the
+// launches have one batch tile; without the tile's arithmetic the compiler's
+// schedule made the d = 2048, dt = 1024 head of one request take 50 us instead
+// of 44).  R consecutive output rows share every load of the inputs (R > 1 when several requests are
 // batched, so the inputs are not re-read per row); S wavefronts of the
 // workgroup split K between them, chunk c going to wavefront c mod S (S = 4
 // for long rows, so that one launch has enough loads in flight to cover HBM
@@ -340,7 +341,7 @@ constexpr int kTargetGroups = 256; // workgroups a launch aims for (one per CU)
 // 1.65e-7, 8192 / 512 / 8 1.76e-7 and 1.69e-7, 2048 / 1024 / 8 1.88e-7 and
 // 2.10e-7).  What bounds it: at d = 4096, dt = 256 the chain of seven launches
 // (~4.5 us each) and, at 32 requests, the towers' inputs, read again by every
-// workgroup; 63.6 us on the vector kernels, 37.0 here.
+// workgroup; 63.6 us on the vector kernels, 35.7 here.
 // The fusion layer's K is nine runs of dt elements, a, b, c, ab, |a - b|, ac,
 // |a - c|, bc, |b - c|, built from the tower outputs while staging: a chunk
 // covers one tower's run and the two it forms with the next tower, so that two
@@ -943,17 +944,17 @@ oda_status check_gate(const oda_gate_desc* g) {
 
 template <int MODE, int R, int S, int BT = kBatchTile>
 void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
-  const int64_t items = a.rows / R * oda::ceil_div(a.B, BT);
+  const int64_t items = a.rows / R;   // B <= BT
   const int64_t groups = S == 1 ? oda::ceil_div(items, kWaves) : items;
   hipLaunchKernelGGL((gate_linear_kernel<MODE, R, S, BT>), dim3((unsigned)groups), dim3(256), 0, stream, a);
 }
 
 // Launch shape of a dense layer.  Four requests or more (five for the MLP
-// head's layer, and see there) take the matrix-core tiles: a call of the App. A.2 head at d =
-// 4096, dt = 256 takes 32 us at 4-16 requests and 37 at 32, against 37 (4), 53
-// (8) and 64 (32) on the vector kernels, whose every few rows re-read all
-// requests' inputs (the d = 4328, dt = 436 head of 3: 42 against 39); the MLP
-// head 12.2 against 12.9 at 32, but 8.4 against 7.4 at 4.
+// head's layer, and see there) take the matrix-core tiles: a call of the App. A.2
+// head at d = 4096, dt = 256 takes 31 us at 4-16 requests and 36 at 32, against
+// 37 (4), 53 (8) and 64 (32) on the vector kernels, whose every few rows re-read
+// all requests' inputs; the MLP head 12.2 against 12.9 at 32, but 8.4 against
+// 7.4 at 4.
 //
 // Smaller batches: K is split over the four wavefronts of a workgroup when
 // rows are long (K >= 4096), or when there are too few rows to occupy the chip
@@ -967,21 +968,13 @@ void launch_linear_rs(const LinArgs& a, hipStream_t stream) {
 template <int MODE>
 void launch_linear(const LinArgs& a, hipStream_t stream) {
   if constexpr (MODE == kMlpHidden) {
-    // A workgroup per row and eight requests where that is faster: a long and
-    // wide layer of up to eight requests streams faster from 16-byte row loads
-    // (5716 -> 928 of five 14.2 us against 15.8), and long rows are too few
-    // tiles, whose wavefronts walk K / 8 elements one wait after the other:
-    // 8192 -> 256 of five 10.4 against 14.9, of sixteen 16.7 against 17.6 (24:
-    // 18.6 against 18.3), 6144 -> 128 of 32 13.7 against 14.9, 8192 -> 512 of
-    // ten 19.0 against 18.2, 4096 -> 256 of six 8.8 against 9.7, of eight 10.4
-    // against 10.2.
-    if (a.B > kSmallBatchMlp) {
-      if (a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20) && a.rows % 2 == 0 && a.rows >= 1024)
-        return launch_linear_rs<MODE, 2, kWaves, 8>(a, stream);
-      if ((a.B <= 8 && (int64_t)a.rows * a.K >= (4 << 20)) || (a.B < 8 && a.K >= 4096) ||
-          (a.K >= 6144 && a.rows * oda::ceil_div(a.B, 8) <= 512))
-        return launch_linear_rs<MODE, 1, kWaves, 8>(a, stream);
-    }
+    // Long rows of a few requests are too few tiles, whose wavefronts walk K / 8
+    // elements one wait after the other; a workgroup per row has less to read:
+    // 8192 -> 256 of five 10.5 us against 14.0, of seven 13.1 against 14.1,
+    // 4096 -> 512 of six 9.7 against 10.0 (of seven 10.4 against 10.0), 5716 ->
+    // 928 of five 13.9 against 13.1, 6144 -> 256 of eight 12.9 against 12.0.
+    if (a.B > kSmallBatchMlp && a.B < 8 && a.K >= 4096 && (int64_t)a.rows * a.B <= 3072)
+      return launch_linear_rs<MODE, 1, kWaves, 8>(a, stream);
   }
   if (a.B > (MODE == kMlpHidden ? kSmallBatchMlp : kSmallBatch)) return launch_tile<MODE>(a, stream);
   const int64_t items = a.rows;

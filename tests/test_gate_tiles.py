@@ -21,9 +21,9 @@ CASES = [
     ("paper", 2052, 260, 33), ("paper", 264, 1028, 4), ("paper", 4096, 132, 65), ("mlp", 4, 4, 5), ("mlp", 100, 28, 8),
     ("mlp", 1020, 2052, 6), ("mlp", 8192, 516, 17), ("mlp", 8192, 516, 7),
     ("mlp", 4100, 1026 * 2, 8),
-    # rows per workgroup instead of tiles, over one and several groups of eight requests, and past the limits
-    ("mlp", 4096, 36, 5), ("mlp", 4100, 516, 7), ("mlp", 6148, 68, 8), ("mlp", 6144, 132, 17), ("mlp", 8196, 256, 16),
-    ("mlp", 6144, 128, 30), ("mlp", 6144, 128, 33), ("mlp", 6140, 64, 9),
+    # a workgroup per row instead of tiles, and past its limits
+    ("mlp", 4096, 36, 5), ("mlp", 4100, 516, 5), ("mlp", 4096, 512, 6), ("mlp", 8196, 436, 7), ("mlp", 4096, 516, 6),
+    ("mlp", 4100, 440, 7), ("mlp", 4092, 64, 7), ("mlp", 6148, 68, 8), ("mlp", 6144, 132, 17), ("mlp", 8196, 256, 16),
     # tiles of sixteen rows and requests
     ("paper", 516, 632, 70), ("paper", 1028, 1028, 40), ("mlp", 260, 1028, 70), ("mlp", 4100, 1028, 40)]
 
